@@ -187,7 +187,9 @@ int no_autotune(const no_net* net, const hz_problem* p, no_prec prec, void* ws_d
  * workgroup *tiles (1; or 2 and more for the weight-stationary form, which keeps the weights of
  * its output channels in LDS across that many tiles; there *stages counts the tiles whose
  * patch loads are in flight together, 2 to 4), as no_autotune chose it or no_set_layer_variant
- * pinned it. Errors: NULL pointer, not a 3x3 layer. */
+ * pinned it. A streamed-weights form (BF16 and FP32 layers of whole 32-channel chunks) reports its
+ * own *tn (16 to 128) and *rows (2 to 16), *tiles 1 and a negative *stages that names it.
+ * Errors: NULL pointer, not a 3x3 layer. */
 int no_layer_variant(const no_net* net, int layer, no_prec prec, int batch, int H, int W, int32_t* tn,
                      int32_t* rows, int32_t* stages, int32_t* tiles);
 
@@ -200,6 +202,7 @@ int no_layer_variant(const no_net* net, int layer, no_prec prec, int batch, int 
  * BF16 where the layer's input is at most 4 whole chunks of 32 channels per part and the weights
  * and patches of all chunks fit in the LDS (then stages 2 or 3, or 4 with at most 2 chunks; 2
  * with 16 rows).
+ * A streamed-weights form is pinned with the four values no_layer_variant reported for it.
  * Thread-safe. */
 int no_set_layer_variant(const no_net* net, int layer, no_prec prec, int batch, int H, int W, int tn, int rows,
                          int stages, int tiles);

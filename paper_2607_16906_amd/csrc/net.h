@@ -52,6 +52,11 @@ struct no_net {
     hz::bf16_t* wt_bf;               // data-gradient packs (flipped / transposed), BF16
     float* wt_f32;
     double* wt_f64;
+    // streamed packs of the 3x3 layers (conv3s_index; layer offsets pk_off): forward, data gradient
+    hz::bf16_t* fs_bf;
+    hz::bf16_t* fst_bf;
+    float* fs_f32;
+    float* fst_f32;
     float* b_f32;                    // biases (FP32; the BF16 path adds them in FP32)
     double* b_f64;
     void* block;

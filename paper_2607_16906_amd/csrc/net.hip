@@ -95,7 +95,8 @@ __global__ void k_repack(const float* __restrict__ theta, const Layer* __restric
                          const int64_t* __restrict__ start, int nl, bf16_t* __restrict__ wb,
                          float* __restrict__ wf, double* __restrict__ wd, float* __restrict__ bf,
                          double* __restrict__ bd, bf16_t* __restrict__ tb, float* __restrict__ tf,
-                         double* __restrict__ td) {
+                         double* __restrict__ td, bf16_t* __restrict__ sb, bf16_t* __restrict__ stb,
+                         float* __restrict__ sf, float* __restrict__ stf) {
     int l = 0;
     while (l + 1 < nl && (int64_t)blockIdx.x >= start[l + 1]) ++l;
     const Layer ly = layers[l];
@@ -141,6 +142,18 @@ __global__ void k_repack(const float* __restrict__ theta, const Layer* __restric
             tf[ly.pk_off + j] = v;
             td[ly.pk_off + j] = (double)v;
         }
+        if (ly.kind == L_CONV3) {
+            const bool fwd = conv3s_layer_ok(ly.cat_cp ? ly.cat_cp : ly.cin_p, ly.cat_cp ? ly.cin_p - ly.cat_cp : 0, ly.cout_p);
+            const bool bwd = conv3s_layer_ok(ly.cout_p, 0, ly.cin_p);
+            if (fwd) {
+                sb[ly.pk_off + conv3s_index<bf16_t>(tap, co, cis, ly.cout_p)] = f2bf(v);
+                sf[ly.pk_off + conv3s_index<float>(tap, co, cis, ly.cout_p)] = v;
+            }
+            if (bwd) {
+                stb[ly.pk_off + conv3s_index<bf16_t>(8 - tap, cis, co, ly.cin_p)] = f2bf(v);
+                stf[ly.pk_off + conv3s_index<float>(8 - tap, cis, co, ly.cin_p)] = v;
+            }
+        }
     }
     if (idx < ly.cout_p) {
         const float b = idx < ly.cout ? theta[ly.b_off + idx] : 0.0f;
@@ -156,7 +169,8 @@ __global__ void k_repack(const float* __restrict__ theta, const Layer* __restric
 static int repack_all(no_net* net, const float* theta, hipStream_t s) {
     hipLaunchKernelGGL(k_repack, dim3((unsigned)net->repack_blocks), dim3(256), 0, s, theta, net->layers_dev,
                        net->repack_start, (int)net->layers.size(), net->w_bf, net->w_f32, net->w_f64, net->b_f32,
-                       net->b_f64, net->wt_bf, net->wt_f32, net->wt_f64);
+                       net->b_f64, net->wt_bf, net->wt_f32, net->wt_f64, net->fs_bf, net->fst_bf, net->fs_f32,
+                       net->fst_f32);
     HZ_LAUNCH_CHECK();
     return HZ_OK;
 }
@@ -341,8 +355,10 @@ static int autotune_impl(const no_net* net, int Hp, int Wp, int batch, const Fwd
     };
     // up (fused form): x1 is unused and U = convT2(up) is computed inside the layer
     // best_out (optional): average time of the chosen variant, ms per launch
+    // head: the layer that carries the fused 1x1 head in a single application; only the forms that
+    // can carry it are candidates
     auto tune_layer = [&](int li, const T* x0, int c0, const T* x1, int c1, T* y, T* pool, int H, int W,
-                          const UpIn* up = nullptr, float* best_out = nullptr) -> int {
+                          const UpIn* up = nullptr, float* best_out = nullptr, bool head = false) -> int {
         const std::array<int, 5> key{li, H, W, batch, (int)prec_of<P>() + (up ? FUSED_KEY : 0)};
         {
             std::lock_guard<std::mutex> g(mnet->tune_mu);
@@ -356,16 +372,16 @@ static int autotune_impl(const no_net* net, int Hp, int Wp, int batch, const Fwd
         // weight-stationary form with 2 ... 16 tiles per block where it applies
         std::vector<ConvCfg> cands;
         for (int tn : {16, 32, 64}) {
-            if (ly.cout_p % tn) continue;
+            if (ly.cout_p % tn || (head && tn != ly.cout_p)) continue;
             for (int rpw : {2, 4}) {
                 for (int ns : {1, 2, 4}) {
                     // chunks per LDS stage: only where there are that many chunks (the plain form)
-                    if (ns > 1 && (up || ns > chunks || !conv3_stages_ok<P>(tn, rpw, ns))) continue;
+                    if (ns > 1 && (up || head || ns > chunks || !conv3_stages_ok<P>(tn, rpw, ns))) continue;
                     ConvCfg cfg{tn, rpw, 1};
                     cfg.ns = ns;
                     cands.push_back(cfg);
                 }
-                if (!up && conv3_ws_ok<P>(tn, rpw, c0, c1, ly.cout_p))
+                if (!up && !head && conv3_ws_ok<P>(tn, rpw, c0, c1, ly.cout_p))
                     for (const auto& tp : {std::array<int, 2>{4, 2}, {8, 3}, {16, 3}, {16, 4}, {32, 4}}) {
                         // (tiles per block, tiles of loads in flight; 4 only with at most 2 chunks;
                         // 16-row tiles with 2)
@@ -377,6 +393,23 @@ static int autotune_impl(const no_net* net, int Hp, int Wp, int batch, const Fwd
                     }
             }
         }
+        if (!up && !std::is_same<P, PolF64>::value && conv3s_layer_ok(c0, c1, ly.cout_p)) {
+            // layers with a streamed pack: the streamed forms that won somewhere in sweeps over 12^2 to
+            // 1088^2 grids and batches of 64 (forms 3, 6, 8, 9, 12 and 13 never did by 3 %). Of the
+            // staged BF16 forms only the weight-stationary one of single-chunk layers is still better
+            // somewhere (32 -> 32 channels at 1088^2: 42 us against 47)
+            const bool keep_ws = std::is_same<P, PolBF16>::value && c0 + c1 == P::CK;
+            std::vector<ConvCfg> kept;
+            for (int id : {7, 2, 5, 1, 11, 4, 10, 9})
+                if (conv3s_form_ok<P>(id, c0, c1, ly.cout_p, 0, head) && (id != 9 || head)) {
+                    ConvCfg cfg{conv3s_form(id).tn(), 2, 1};
+                    cfg.st = id;
+                    kept.push_back(cfg);
+                }
+            for (const ConvCfg& cfg : cands)
+                if (kept.empty() || (keep_ws && cfg.tpb > 1)) kept.push_back(cfg);
+            cands.swap(kept);
+        }
         for (const ConvCfg& cfg : cands) {
             auto run = [&]() {
                 if (up)
@@ -384,7 +417,7 @@ static int autotune_impl(const no_net* net, int Hp, int Wp, int batch, const Fwd
                                               y, ly.cout_p, H, W, batch, nullptr, s, cfg);
                 return launch_conv3<P>(x0, c0, x1, c1, packed_w<P>(net, ly), packed_b<P>(net, ly), y,
                                        ly.cout_p, pool, H, W, batch, true, nullptr, s, Conv3Out(), cfg,
-                                       (Acc*)b.splitbuf);
+                                       (Acc*)b.splitbuf, streamed_w<P>(net, ly));
             };
             HZ_TRY(run());
             HZ_TRY(hold());
@@ -471,7 +504,8 @@ static int autotune_impl(const no_net* net, int Hp, int Wp, int batch, const Fwd
             rc = tune_layer(li + 1, (const T*)b.E[l], ce, (const T*)b.U[l], ce, (T*)b.T1d[l], nullptr, H, W);
         }
         if (rc == HZ_OK)
-            rc = tune_layer(li + 2, (const T*)b.T1d[l], Ls[li + 2].cin_p, nullptr, 0, (T*)b.D[l], nullptr, H, W);
+            rc = tune_layer(li + 2, (const T*)b.T1d[l], Ls[li + 2].cin_p, nullptr, 0, (T*)b.D[l], nullptr, H, W,
+                            nullptr, nullptr, l == 0 && batch == 1 && Ls[li + 2].cout_p <= 64);
         li += 3;
     }
     (void)hipEventDestroy(e0);
@@ -565,8 +599,9 @@ extern "C" int no_net_create(const no_arch* a, const float* theta, void* stream,
     }
     net->a = *a;
     const size_t nl = net->layers.size();
-    const size_t bytes = 2 * net->pk_total * (2 + 4 + 8) + net->bias_total * (4 + 8) + nl * sizeof(Layer) +
-                         (nl + 1) * sizeof(int64_t) + 10 * 256;
+    const size_t fs = a->kind == NO_ARCH_UNET3 ? net->pk_total : 0;   // streamed packs
+    const size_t bytes = 2 * net->pk_total * (2 + 4 + 8) + 2 * fs * (2 + 4) + net->bias_total * (4 + 8) +
+                         nl * sizeof(Layer) + (nl + 1) * sizeof(int64_t) + 14 * 256;
     if (hipMalloc(&net->block, bytes) != hipSuccess) {
         delete net;
         set_error("no_net_create: hipMalloc failed");
@@ -581,6 +616,10 @@ extern "C" int no_net_create(const no_arch* a, const float* theta, void* stream,
     net->wt_bf = c.take<bf16_t>(net->pk_total);
     net->wt_f32 = c.take<float>(net->pk_total);
     net->wt_f64 = c.take<double>(net->pk_total);
+    net->fs_bf = c.take<bf16_t>(fs);
+    net->fst_bf = c.take<bf16_t>(fs);
+    net->fs_f32 = c.take<float>(fs);
+    net->fst_f32 = c.take<float>(fs);
     net->layers_dev = c.take<Layer>(nl);
     net->repack_start = c.take<int64_t>(nl + 1);
     std::vector<int64_t> start(nl + 1, 0);
@@ -724,7 +763,7 @@ static int layer_impl(const no_net* net, int layer, int batch, int H, int W, con
         if (!ws || ws_bytes < need) cfg.ksplit = 1;
         return launch_conv3<P>((const T*)x0, c0, (const T*)x1, c1, packed_w<P>(net, ly), packed_b<P>(net, ly),
                                (T*)y, ly.cout_p, (T*)pool, H, W, batch, true, nullptr, s, Conv3Out(), cfg,
-                               (typename P::Acc*)ws);
+                               (typename P::Acc*)ws, streamed_w<P>(net, ly));
     }
     return launch_convT2<P>((const T*)x0, ly.cin_p, packed_w<P>(net, ly), packed_b<P>(net, ly), (T*)y, ly.cout_p,
                             H, W, batch, nullptr, s);
@@ -759,8 +798,8 @@ extern "C" int no_layer_variant(const no_net* net, int layer, no_prec prec, int 
                  "no_layer_variant: not a 3x3 layer");
     const ConvCfg c = net_cfg(net, layer, H, W, batch, prec);
     *tn = c.tn;
-    *rows = 4 * (c.rpw == 4 ? 4 : 2);
-    *stages = c.ns;
+    *rows = c.st > 0 ? conv3s_form(c.st).th() : 4 * (c.rpw == 4 ? 4 : 2);
+    *stages = c.st > 0 ? -c.st : c.ns;
     *tiles = c.tpb > 1 ? c.tpb : 1;
     return HZ_OK;
 }
@@ -772,12 +811,20 @@ extern "C" int no_set_layer_variant(const no_net* net, int layer, no_prec prec, 
     HZ_CHECK_ARG(layer >= 0 && layer < (int)net->layers.size() && net->layers[layer].kind == L_CONV3,
                  "no_set_layer_variant: not a 3x3 layer");
     HZ_CHECK_ARG(prec == NO_BF16 || prec == NO_FP32 || prec == NO_FP64, "no_set_layer_variant: bad precision");
-    HZ_CHECK_ARG((tn == 16 || tn == 32 || tn == 64) && net->layers[layer].cout_p % tn == 0 && (rows == 8 || rows == 16),
-                 "no_set_layer_variant: tn must be 16, 32 or 64 and divide the output channels, rows 8 or 16");
-    const int rpw = rows / 4;
     const Layer& ly = net->layers[layer];
     const int c0 = ly.cat_cp > 0 ? ly.cat_cp : ly.cin_p, c1 = ly.cat_cp > 0 ? ly.cin_p - ly.cat_cp : 0;
-    if (tiles > 1) {
+    const bool streamed = stages < 0 && stages >= -CONV3S_NFORM;
+    HZ_CHECK_ARG(streamed || ((tn == 16 || tn == 32 || tn == 64) && ly.cout_p % tn == 0 && (rows == 8 || rows == 16)),
+                 "no_set_layer_variant: tn must be 16, 32 or 64 and divide the output channels, rows 8 or 16");
+    const int rpw = rows / 4;
+    if (streamed) {
+        const Conv3sForm f = conv3s_form(-stages);
+        const bool ok = prec == NO_BF16   ? conv3s_form_ok<PolBF16>(-stages, c0, c1, ly.cout_p, 0, false)
+                        : prec == NO_FP32 ? conv3s_form_ok<PolF32>(-stages, c0, c1, ly.cout_p, 0, false)
+                                          : false;
+        HZ_CHECK_ARG(ok && tn == f.tn() && rows == f.th() && tiles == 1,
+                     "no_set_layer_variant: not a streamed form of this layer");
+    } else if (tiles > 1) {
         HZ_CHECK_ARG(tiles <= 64 && prec == NO_BF16 && conv3_ws_ok<PolBF16>(tn, rpw, c0, c1, ly.cout_p) &&
                          stages >= 2 && stages <= (rpw == 4 ? 2 : c0 + c1 <= 2 * PolBF16::CK ? 4 : 3),
                      "no_set_layer_variant: tiles must be 1, or 2..64 for the weight-stationary BF16 form (at most "
@@ -791,8 +838,9 @@ extern "C" int no_set_layer_variant(const no_net* net, int layer, no_prec prec, 
     HZ_CHECK_ARG(batch >= 1 && H >= 1 && W >= 1, "no_set_layer_variant: bad size");
     no_net* mnet = const_cast<no_net*>(net);
     std::lock_guard<std::mutex> g(mnet->tune_mu);
-    ConvCfg c{tn, rpw, 1};
-    c.ns = stages;
+    ConvCfg c{tn, streamed ? 2 : rpw, 1};
+    c.ns = streamed ? 1 : stages;
+    c.st = streamed ? -stages : 0;
     c.tpb = tiles > 1 ? tiles : 0;
     mnet->tuned[{layer, H, W, batch, (int)prec}] = c;
     mnet->tune_gen.fetch_add(1);

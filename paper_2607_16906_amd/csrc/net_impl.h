@@ -191,6 +191,22 @@ inline const typename P::T* packed_wt(const no_net* net, const Layer& ly) {
     else if constexpr (sizeof(typename P::T) == 4) return net->wt_f32 + ly.pk_off;
     else return net->wt_f64 + ly.pk_off;
 }
+// streamed packs of a 3x3 layer (NULL where it has none): forward, data gradient
+template <class P>
+inline const void* streamed_w(const no_net* net, const Layer& ly) {
+    const int c0 = ly.cat_cp ? ly.cat_cp : ly.cin_p;
+    if (ly.kind != L_CONV3 || !conv3s_layer_ok(c0, ly.cin_p - c0, ly.cout_p)) return nullptr;
+    if constexpr (sizeof(typename P::T) == 2) return net->fs_bf + ly.pk_off;
+    else if constexpr (sizeof(typename P::T) == 4) return net->fs_f32 + ly.pk_off;
+    else return nullptr;
+}
+template <class P>
+inline const void* streamed_wt(const no_net* net, const Layer& ly) {
+    if (ly.kind != L_CONV3 || !conv3s_layer_ok(ly.cout_p, 0, ly.cin_p)) return nullptr;
+    if constexpr (sizeof(typename P::T) == 2) return net->fst_bf + ly.pk_off;
+    else if constexpr (sizeof(typename P::T) == 4) return net->fst_f32 + ly.pk_off;
+    else return nullptr;
+}
 template <class P>
 inline const typename P::Acc* packed_b(const no_net* net, const Layer& ly) {
     if constexpr (sizeof(typename P::Acc) == 4) return net->b_f32 + ly.bias_off;
@@ -249,12 +265,12 @@ inline int unet_body(const no_net* net, const FwdBufs& b, int Hp, int Wp, int ba
         const T* in = l == 0 ? (const T*)b.X : (const T*)b.P[l];
         HZ_TRY(launch_conv3<P>(in, la.cin_p, nullptr, 0, packed_w<P>(net, la), packed_b<P>(net, la), (T*)b.T1[l],
                                la.cout_p, nullptr, H, W, batch, true, skip, s, Conv3Out(),
-                               net_cfg(net, li - 2, H, W, batch, prec_of<P>()), sb));
+                               net_cfg(net, li - 2, H, W, batch, prec_of<P>()), sb, streamed_w<P>(net, la)));
         T* pool = l + 1 < lv ? (T*)b.P[l + 1] : nullptr;
         const bool last = lv == 1 && head;   // a one-level net ends here
         HZ_TRY(launch_conv3<P>((const T*)b.T1[l], lb.cin_p, nullptr, 0, packed_w<P>(net, lb), packed_b<P>(net, lb),
                                (T*)b.E[l], lb.cout_p, pool, H, W, batch, true, skip, s, last ? *head : Conv3Out(),
-                               net_cfg(net, li - 1, H, W, batch, prec_of<P>()), sb));
+                               net_cfg(net, li - 1, H, W, batch, prec_of<P>()), sb, streamed_w<P>(net, lb)));
     }
     const T* Dn = (const T*)b.E[lv - 1];
     for (int l = lv - 2; l >= 0; --l) {
@@ -277,12 +293,13 @@ inline int unet_body(const no_net* net, const FwdBufs& b, int Hp, int Wp, int ba
                                     lu.cout_p, H / 2, W / 2, batch, skip, s));
             HZ_TRY(launch_conv3<P>((const T*)b.E[l], ce, (const T*)b.U[l], ce, packed_w<P>(net, la),
                                    packed_b<P>(net, la), (T*)b.T1d[l], la.cout_p, nullptr, H, W, batch, true, skip,
-                                   s, Conv3Out(), net_cfg(net, li - 2, H, W, batch, prec_of<P>()), sb));
+                                   s, Conv3Out(), net_cfg(net, li - 2, H, W, batch, prec_of<P>()), sb,
+                                   streamed_w<P>(net, la)));
         }
         const bool last = l == 0 && head;
         HZ_TRY(launch_conv3<P>((const T*)b.T1d[l], lb.cin_p, nullptr, 0, packed_w<P>(net, lb), packed_b<P>(net, lb),
                                (T*)b.D[l], lb.cout_p, nullptr, H, W, batch, true, skip, s, last ? *head : Conv3Out(),
-                               net_cfg(net, li - 1, H, W, batch, prec_of<P>()), sb));
+                               net_cfg(net, li - 1, H, W, batch, prec_of<P>()), sb, streamed_w<P>(net, lb)));
         Dn = (const T*)b.D[l];
     }
     return HZ_OK;

@@ -143,6 +143,7 @@ struct ConvCfg {
     int ksplit = 1;
     int fuse = 0;   // decoder layer: take the fused form (transposed convolution inside, UpIn)
     int ns = 1;     // input-channel chunks per LDS stage (1, 2 or 4; BF16 only, same result bits)
+    int st = 0;     // > 0: streamed-weights form (conv3s_form); tn is then its channel tile
     int tpb = 0;    // > 1: weight-stationary form with tpb pixel tiles per block (BF16, conv3_ws_ok);
                     // ns is then the number of tiles whose loads are in flight (2, 3 or 4)
 };
@@ -201,13 +202,84 @@ struct UpIn {
 };
 constexpr int UP_CDMAX = 128;   // largest coarse channel count of the fused form
 
+// Streamed-weights 3x3 convolution (net_stream.h). Forms (id, 16-channel blocks per wavefront, rows
+// per wavefront, wavefronts along channels, wavefronts along rows).
+#define HZ_CONV3S_FORMS(F) \
+    F(1, 1, 2, 4, 1) F(2, 1, 4, 4, 1) F(3, 1, 8, 4, 1) F(4, 2, 8, 4, 1) F(5, 1, 4, 2, 2) F(6, 1, 8, 2, 2) F(7, 2, 4, 2, 2) \
+    F(8, 2, 8, 2, 2) F(9, 2, 2, 1, 4) F(10, 2, 4, 1, 4) F(11, 1, 2, 2, 2) F(12, 1, 2, 1, 4) F(13, 1, 4, 1, 4)
+constexpr int CONV3S_NFORM = 13;
+struct Conv3sForm {
+    int ncb, rpw, wc, wr;
+    constexpr int tn() const { return 16 * ncb * wc; }   // output channels per block
+    constexpr int th() const { return rpw * wr; }        // pixel rows per block (16 columns)
+};
+constexpr Conv3sForm conv3s_form(int id) {
+#define HZ_CSF(ID, A, B, C, D) \
+    if (id == ID) return Conv3sForm{A, B, C, D};
+    HZ_CONV3S_FORMS(HZ_CSF)
+#undef HZ_CSF
+    return Conv3sForm{0, 0, 0, 0};
+}
+// Layers that have a streamed pack: whole chunks of 32 input channels in both parts.
+constexpr bool conv3s_layer_ok(int c0, int c1, int cout_p) {
+    return c0 > 0 && c0 % 32 == 0 && c1 % 32 == 0 && cout_p % 16 == 0;
+}
+// Whether form `id` takes the layer: its channel blocks divide every output part, and a fused head
+// sees all channels in one wavefront.
+template <class P>
+constexpr bool conv3s_form_ok(int id, int c0, int c1, int cout_p, int split, bool head) {
+    const Conv3sForm f = conv3s_form(id);
+    if (f.ncb == 0 || !conv3s_layer_ok(c0, c1, cout_p)) return false;
+    if (std::is_same<P, PolF64>::value) return false;
+    if (cout_p % f.tn() || split % f.tn()) return false;
+    return !head || (f.wc == 1 && cout_p == f.tn());
+}
+// Position of weight (tap, co, ci) in a streamed pack of T: operands of 1 KB [chunk][channel block][tap],
+// 16 bytes per lane (row co % 16, lane group lg). BF16: chunks of 32, lane group lg holds channels
+// 8 lg ..; FP32: chunks of 16, it holds channels lg, 4 + lg, 8 + lg, 12 + lg.
+template <typename T>
+__host__ __device__ constexpr int64_t conv3s_index(int tap, int co, int ci, int cout_p) {
+    constexpr int CK = 64 / (int)sizeof(T), VE = 16 / (int)sizeof(T);
+    const int c = ci % CK;
+    const int lg = sizeof(T) == 2 ? c / VE : c % 4, e = sizeof(T) == 2 ? c % VE : c / 4;
+    return (((int64_t)(ci / CK) * (cout_p / 16) + co / 16) * 9 + tap) * (1024 / (int)sizeof(T)) +
+           (lg * 16 + co % 16) * VE + e;
+}
+template <class P>
+struct Conv3sArgs {
+    const typename P::T* x0;
+    int c0;
+    const typename P::T* x1;
+    int c1;
+    const void* wf;      // streamed pack (conv3s_index)
+    const float* bias;
+    typename P::T* y;
+    int cout_p;
+    typename P::T* ypool;
+    int H, W, batch, relu;
+    const int* skip;
+    Conv3Out ex;
+};
+template <class P>
+int launch_conv3s(int form, const Conv3sArgs<P>& g, hipStream_t s);
+
+// Consecutive workgroups are dispatched round-robin over the 8 XCDs, each with its own L2.
+// Renumber the physical block id so that the blocks one XCD runs form one contiguous range of
+// the logical order (in which blocks that read the same input tile are neighbours).
+__device__ __forceinline__ int xcd_linear(int p, int n) {
+    const int q = n / 8, r = n % 8;
+    const int k = p % 8, i = p / 8;
+    return k * q + (k < r ? k : r) + i;
+}
+
 // Host-side launch helpers (defined in net_fwd.hip), one per precision.
-// conv3: y = act(conv3x3(concat[x0, x1]) + b) (+ pooled copy); batch samples along grid z.
+// conv3: y = act(conv3x3(concat[x0, x1]) + b) (+ pooled copy); batch samples along grid z. wf: the
+// layer's streamed pack, if it has one.
 template <class P>
 int launch_conv3(const typename P::T* x0, int c0, const typename P::T* x1, int c1, const typename P::T* w,
                  const typename P::Acc* bias, typename P::T* y, int cout_p, typename P::T* ypool, int H, int W,
                  int batch, bool relu, const int* skip, hipStream_t s, Conv3Out ex = Conv3Out(),
-                 ConvCfg cfg = ConvCfg(), typename P::Acc* splitbuf = nullptr);
+                 ConvCfg cfg = ConvCfg(), typename P::Acc* splitbuf = nullptr, const void* wf = nullptr);
 // Ragged-batch versions: one launch over a job table (3x3: tiles of 4 rpw rows x 16 columns, rpw 2,
 // or 4 with tn 32 in BF16).
 template <class P>
@@ -228,18 +300,6 @@ template <class P>
 constexpr bool ws_jobs_ok(int c0, int c1, int cout_p) {
     return conv3_ws_ok<P>(WSJ_TN, WSJ_RPW, c0, c1, cout_p) && c0 + c1 <= 2 * P::CK;
 }
-// The data gradient of training (split output, masks, no bias) in the weight-stationary form:
-// BF16, an input of 1 or 2 chunks, WSJ_TN-channel blocks that both output parts divide, 16 x 16
-// tiles; y0 / y1 / masks as Conv3Out's split and masks, samples along grid z.
-template <class P>
-constexpr bool conv3_ws_dgrad_ok(int c0, int cout_p, int split) {
-    return conv3_ws_ok<P>(WSJ_TN, WSJ_RPW, c0, 0, cout_p) && c0 <= 2 * P::CK && split % WSJ_TN == 0 &&
-           (cout_p - split) % WSJ_TN == 0;
-}
-template <class P>
-int launch_conv3_ws_dgrad(const typename P::T* x0, int c0, const typename P::T* w, typename P::T* y0, int cout_p,
-                          int H, int W, int batch, int split, typename P::T* y1, const typename P::T* mask0,
-                          const typename P::T* mask1, hipStream_t s);
 template <class P>
 int launch_conv3_ws_jobs(const TileJob* jobs, int njobs, const LayerIO* io, const typename P::T* w,
                          const typename P::Acc* bias, int c0, int c1, int cout_p, bool pool,

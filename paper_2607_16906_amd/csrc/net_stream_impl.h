@@ -1,0 +1,50 @@
+// Launcher of the streamed-weights 3x3 convolution, instantiated once per precision.
+#pragma once
+
+#include "net_stream.h"
+
+namespace hz {
+
+template <class S, int NCB, int RPW, int WC, int WR>
+static int launch_form(const Conv3sArgs<typename S::P>& g, hipStream_t s) {
+    constexpr int TN = 16 * NCB * WC, TH = RPW * WR;
+    const int64_t nblk = (int64_t)((g.W + 15) / 16) * ((g.H + TH - 1) / TH) * (g.cout_p / TN) * g.batch;
+    if (nblk <= 0 || nblk > INT32_MAX) {
+        set_error("conv3: grid too large");
+        return HZ_ERR_ARG;
+    }
+    const dim3 grid((unsigned)nblk), block(64 * WC * WR);
+#define HZ_CS(E)                                                                                                \
+    hipLaunchKernelGGL((k_conv3s<S, NCB, RPW, WC, WR, E>), grid, block, 0, s, g.x0, g.c0, g.x1, g.c1, g.wf, g.bias, \
+                       g.y, g.cout_p, g.ypool, g.H, g.W, g.relu, g.skip, g.ex)
+    if (g.ex.head_w) {
+        if constexpr (WC == 1) HZ_CS(CS_HEAD);
+    } else if (g.ex.split || g.ex.mask0_ || g.ex.mask1_) {
+        HZ_CS(CS_MASKED);
+    } else if (g.ypool) {
+        HZ_CS(CS_POOL);
+    } else {
+        HZ_CS(CS_PLAIN);
+    }
+#undef HZ_CS
+    HZ_LAUNCH_CHECK();
+    return HZ_OK;
+}
+
+template <class S>
+static int launch_conv3s_any(int form, const Conv3sArgs<typename S::P>& g, hipStream_t s) {
+    if (!conv3s_form_ok<typename S::P>(form, g.c0, g.c1, g.cout_p, g.ex.split, g.ex.head_w != nullptr) || !g.wf) {
+        set_error("conv3: the streamed form does not take these channels");
+        return HZ_ERR_ARG;
+    }
+    switch (form) {
+#define HZ_CSF(ID, NCB, RPW, WC, WR) \
+    case ID: return launch_form<S, NCB, RPW, WC, WR>(g, s);
+        HZ_CONV3S_FORMS(HZ_CSF)
+#undef HZ_CSF
+    }
+    set_error("conv3: unknown streamed form");
+    return HZ_ERR_ARG;
+}
+
+}  // namespace hz

@@ -1106,13 +1106,9 @@ static int dgrad_conv3(const no_net* net, const Layer& ly, const typename P::T* 
     ex.y1_ = y1;
     ex.mask0_ = mask0;
     ex.mask1_ = mask1;
-    // output channels of the data gradient = stored input channels of the layer; BF16 layers whose
-    // gradient has 1 or 2 chunks take the weight-stationary form (the same result bits)
-    if (conv3_ws_dgrad_ok<P>(ly.cout_p, ly.cin_p, ly.cat_cp))
-        return launch_conv3_ws_dgrad<P>(G, ly.cout_p, packed_wt<P>(net, ly), y0, ly.cin_p, H, W, B, ly.cat_cp, y1,
-                                        mask0, mask1, s);
+    // output channels of the data gradient = stored input channels of the layer
     return launch_conv3<P>(G, ly.cout_p, nullptr, 0, packed_wt<P>(net, ly), nullptr, y0, ly.cin_p, nullptr, H, W, B,
-                           false, nullptr, s, ex);
+                           false, nullptr, s, ex, ConvCfg(), nullptr, streamed_wt<P>(net, ly));
 }
 
 template <class P>
@@ -1309,7 +1305,7 @@ static int loss_backward_impl(const no_net* net, int B, const hz_problem* const*
             HZ_TRY(launch_conv3<P>((const T*)t.f.E[l], lu.cout_p, (const T*)t.f.U[l], lu.cout_p, packed_w<P>(net, la),
                                    packed_b<P>(net, la), (T*)t.f.T1d[l], la.cout_p, nullptr, H, W, B, true, nullptr,
                                    s, Conv3Out(), net_cfg(net, dec_a[l], H, W, B, prec_of<P>()),
-                                   (Acc*)t.f.splitbuf));
+                                   (Acc*)t.f.splitbuf, streamed_w<P>(net, la)));
         }
         const T* A1 = (const T*)t.f.T1d[l];
         HZ_TRY(wgrad_conv3<P>(lb, t.gB[l], A1, lb.cin_p, nullptr, 0, H, W, B, t, grad, s));
@@ -1331,7 +1327,8 @@ static int loss_backward_impl(const no_net* net, int B, const hz_problem* const*
         if (recompute)   // the level's first-convolution output, as the forward pass made it
             HZ_TRY(launch_conv3<P>(in, la.cin_p, nullptr, 0, packed_w<P>(net, la), packed_b<P>(net, la),
                                    (T*)t.f.T1[l], la.cout_p, nullptr, H, W, B, true, nullptr, s, Conv3Out(),
-                                   net_cfg(net, enc_a[l], H, W, B, prec_of<P>()), (Acc*)t.f.splitbuf));
+                                   net_cfg(net, enc_a[l], H, W, B, prec_of<P>()), (Acc*)t.f.splitbuf,
+                                   streamed_w<P>(net, la)));
         const T* A1 = (const T*)t.f.T1[l];
         HZ_TRY(wgrad_conv3<P>(lb, t.gB[l], A1, lb.cin_p, nullptr, 0, H, W, B, t, grad, s));
         HZ_TRY(dgrad_conv3<P>(net, lb, t.gB[l], H, W, B, t.gA[l], nullptr, A1, nullptr, s));
