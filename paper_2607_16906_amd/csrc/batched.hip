@@ -428,33 +428,40 @@ struct HostTables {
     std::vector<std::vector<TileJob>> cjobs;
     std::vector<int> tn, rpw;
     std::vector<char> ws;   // layer in the weight-stationary form
+    std::vector<int> st;    // streamed-weights form of a 3x3 layer (0: none)
 };
 
-// Launch form of a 3x3 layer over a ragged batch with `tiles` 16 x 16 pixel tiles in all: in BF16
-// the weight-stationary form with 32-channel blocks where it applies (layers of at most two input
-// chunks), with enough tiles per block to pipeline them and enough blocks to fill the GPU, else
-// 16 x 16 tiles with 32-channel blocks; FP32 / FP64 keep 8 x 16 tiles (conv3_batch_tn).
+// Launch form of a 3x3 layer over a ragged batch with `tiles16` 16 x 16 and `tiles8` 8 x 16 pixel tiles.
+// BF16: the first layer, and single-chunk layers without a pooled output or head, take the
+// weight-stationary form with 32-channel blocks, with enough tiles per block to pipeline them and
+// enough blocks to fill the GPU. The other layers of whole 32-channel chunks, and all of them in FP32,
+// take the streamed-weights forms (st): 64 -> 64 channels over 557k pixels 76 -> 53 us, 128 -> 64 125 ->
+// 87 us, the level-0 layer with the head 102 -> 61 us, the pooled one 110 -> 66 us. The rest run
+// 16 x 16 tiles with 32-channel blocks (BF16) or 8 x 16 tiles (conv3_batch_tn).
 template <class P>
-static void batch_conv3_form(const Layer& ly, int c1, int64_t tiles16, int64_t tiles8, bool head, int& tn, int& rpw,
-                             int& tpb) {
+static void batch_conv3_form(const Layer& ly, int c1, int64_t tiles16, int64_t tiles8, int st, bool pool, bool head,
+                             int& tn, int& rpw, int& tpb) {
     tpb = 0;
-    if (std::is_same<P, PolBF16>::value && ly.cout_p % 32 == 0) {
+    const bool wide = std::is_same<P, PolBF16>::value && ly.cout_p % 32 == 0 && !head;
+    if (wide && !(st && (pool || ly.cin_p > P::CK)) && ws_jobs_ok<P>(ly.cin_p - c1, c1, ly.cout_p)) {
         const int64_t ncb = ly.cout_p / WSJ_TN;
-        if (ws_jobs_ok<P>(ly.cin_p - c1, c1, ly.cout_p) && (!head || ly.cout_p == WSJ_TN)) {
-            int t = 32;
-            while (t > 4 && (tiles16 + t - 1) / t * ncb < 1024) t /= 2;
-            if ((tiles16 + t - 1) / t * ncb >= 256) {
-                tn = WSJ_TN;
-                rpw = WSJ_RPW;
-                tpb = t;
-                return;
-            }
-        }
-        if (!head && tiles16 * (ly.cout_p / 32) >= 512) {
-            tn = 32;
-            rpw = 4;
+        int t = 32;
+        while (t > 4 && (tiles16 + t - 1) / t * ncb < 1024) t /= 2;
+        if ((tiles16 + t - 1) / t * ncb >= 256) {
+            tn = WSJ_TN;
+            rpw = WSJ_RPW;
+            tpb = t;
             return;
         }
+    }
+    if (st) {
+        tn = conv3s_form(st).tn();
+        return;
+    }
+    if (wide && tiles16 * (ly.cout_p / 32) >= 512) {
+        tn = 32;
+        rpw = 4;
+        return;
     }
     tn = head ? ly.cout_p : conv3_batch_tn(ly.cout_p, tiles8);
     rpw = 2;
@@ -489,6 +496,7 @@ static void build_tables(const BatchPlan<P>& B, const no_net* net, const std::ve
     h.tn.assign(nl, 16);
     h.rpw.assign(nl, 2);
     h.ws.assign(nl, 0);
+    h.st.assign(nl, 0);
     for (int li = 0; li < nl - 1; ++li) {
         const Layer& ly = net->layers[li];
         const int l = lvl[li];
@@ -500,7 +508,7 @@ static void build_tables(const BatchPlan<P>& B, const no_net* net, const std::ve
             tiles16 += (int64_t)((W + 15) / 16) * ((H + 15) / 16);
         }
         const bool fhead = li == nl - 2 && head_fused(net);
-        int tn = 16, rpw = 2, tpb = 0;
+        int tn = 16, rpw = 2, tpb = 0, st = 0;
         if (convT) {
             tn = convT2_batch_tn(ly.cout_p);
             // weight-stationary form where the input channels fit one stage: 4-32 row segments per
@@ -512,11 +520,22 @@ static void build_tables(const BatchPlan<P>& B, const no_net* net, const std::ve
                 if ((tiles + t - 1) / t * ncb >= 256) tpb = t;
             }
         } else {
-            batch_conv3_form<P>(ly, ly.cat_cp ? ly.cin_p - ly.cat_cp : 0, tiles16, tiles, fhead, tn, rpw, tpb);
+            const int c1 = ly.cat_cp ? ly.cin_p - ly.cat_cp : 0;
+            if (streamed_w<P>(net, ly))
+                st = conv3s_pick<P>(ly.cin_p - c1, c1, ly.cout_p, 0, fhead, [&](int th) {
+                    int64_t n = 0;
+                    for (int s : active)
+                        n += (int64_t)(((B.S[s].Wp >> l) + 15) / 16) * (((B.S[s].Hp >> l) + th - 1) / th);
+                    return n;
+                });
+            batch_conv3_form<P>(ly, c1, tiles16, tiles, st, role[li] == 1 && l + 1 < net->a.levels, fhead, tn, rpw, tpb);
+            if (tpb > 0) st = 0;
         }
         h.tn[li] = tn;
         h.rpw[li] = rpw;
         h.ws[li] = tpb > 0;
+        h.st[li] = st;
+        const int th = st ? conv3s_form(st).th() : 4 * rpw;   // tile rows of a 3x3 layer
         for (int s = 0; s < nsys; ++s) {
             const FwdBufs& fb = B.S[s].fb;
             LayerIO& io = h.io[li][s];
@@ -561,7 +580,7 @@ static void build_tables(const BatchPlan<P>& B, const no_net* net, const std::ve
                     for (int co = 0; co < ly.cout_p; co += tn)
                         h.cjobs[li].push_back(TileJob{s, co, t0, std::min(nt, t0 + tpb)});
             } else {
-                for (int ty = 0; ty < H; ty += 4 * rpw)
+                for (int ty = 0; ty < H; ty += th)
                     for (int tx = 0; tx < W; tx += 16)
                         for (int co = 0; co < ly.cout_p; co += tn) h.cjobs[li].push_back(TileJob{s, co, ty, tx});
             }
@@ -614,9 +633,16 @@ static int net_step(const BatchPlan<P>& B, const HostTables<P>& h, const no_net*
             const int c1 = ly.cat_cp ? ly.cin_p - ly.cat_cp : 0;
             const bool pool = role[li] == 1 && lvl[li] + 1 < net->a.levels;
             HZ_TRY(launch_conv3_ws_jobs<P>(t.cjobs[li], nj, t.io[li], packed_w<P>(net, ly), packed_b<P>(net, ly),
-                                           ly.cin_p - c1, c1, ly.cout_p, pool, hd ? packed_w<P>(net, lh) : nullptr,
-                                           hd ? packed_b<P>(net, lh) : nullptr, col, std::is_same<C, double2>::value,
-                                           s));
+                                           ly.cin_p - c1, c1, ly.cout_p, pool, s));
+        } else if (h.st[li]) {
+            if constexpr (!std::is_same<P, PolF64>::value) {
+                const int c1 = ly.cat_cp ? ly.cin_p - ly.cat_cp : 0;
+                const bool pool = role[li] == 1 && lvl[li] + 1 < net->a.levels;
+                HZ_TRY(launch_conv3s_jobs<P>(h.st[li], t.cjobs[li], nj, t.io[li], streamed_w<P>(net, ly),
+                                             packed_b<P>(net, ly), ly.cin_p - c1, c1, ly.cout_p, pool,
+                                             hd ? packed_w<P>(net, lh) : nullptr, hd ? packed_b<P>(net, lh) : nullptr,
+                                             col, std::is_same<C, double2>::value, s));
+            }
         } else if (hd) {
             HZ_TRY(launch_conv3_jobs_head<P>(t.cjobs[li], nj, t.io[li], packed_w<P>(net, ly), packed_b<P>(net, ly),
                                              ly.cin_p, 0, ly.cout_p, packed_w<P>(net, lh), packed_b<P>(net, lh), col,

@@ -562,22 +562,20 @@ __global__ __launch_bounds__(CT) void k_conv3(const typename P::T* __restrict__ 
 // oldest tile alone while K - 1 tiles of loads stay in flight. One barrier per step. Every output
 // is accumulated chunk by chunk and tap by tap as in conv3_tile (same result bits as the other
 // variants). Plain epilogue: bias, ReLU, optional 2 x 2 average pool.
-// With HEAD (TN == cout_p) the epilogue is the fused 1x1 head of conv3_tile instead (ex.head_*).
 constexpr int WS_THREADS = 2 * CT;
 // One block: output channels [co0, co0 + TN) of tiles [t_beg, t_end) of one sample (xs0, xs1, ys,
 // yps already point at the sample; tiles row-major over the image, TW wide and 4 RPW high).
-template <class P, int TN, bool POOL, int RPW, int WCH, int K, bool HEAD, bool SMALL = false>
+template <class P, int TN, bool POOL, int RPW, int WCH, int K, bool SMALL = false>
 __device__ __forceinline__ void conv3_ws_body(const typename P::T* __restrict__ xs0, int c0,
                                               const typename P::T* __restrict__ xs1, int c1,
                                               const typename P::T* __restrict__ w,
                                               const typename P::Acc* __restrict__ bias,
                                               typename P::T* __restrict__ ys, int cout_p,
                                               typename P::T* __restrict__ yps, int H, int W, int relu, int co0,
-                                              int t_beg, int t_end, int skipped, const Conv3Out& ex) {
+                                              int t_beg, int t_end, int skipped) {
     using T = typename P::T;
     using Acc = typename P::Acc;
     using AccV = typename P::AccV;
-    static_assert(!HEAD || !POOL, "the fused head has no pooled output");
     static_assert(!SMALL || WCH == 1, "an input of one k-group per tap is one chunk");
     constexpr int TH_ = 4 * RPW;
     constexpr int PS = pix_stride<P>();
@@ -677,8 +675,7 @@ __device__ __forceinline__ void conv3_ws_body(const typename P::T* __restrict__ 
     __syncthreads();
 
     // compute wavefronts: tile t from LDS buffer b, outputs to memory
-    Acc bpre[NCB][4], hw0[NCB][4], hw1[NCB][4];
-    Acc hb0 = Acc(0), hb1 = Acc(0);
+    Acc bpre[NCB][4];
     auto compute = [&](int t, int b) {
         AccV acc[RPW][NCB];
 #pragma unroll
@@ -697,42 +694,6 @@ __device__ __forceinline__ void conv3_ws_body(const typename P::T* __restrict__ 
         // (ty0 + RPW wv + pb, tx0 + lr)
         const int ty0 = (t / ntx) * TH_, tx0 = (t % ntx) * TW;
         const int gx = tx0 + lr;
-        if constexpr (HEAD) {   // as conv3_tile's fused head: rounded activations, then the 1x1 head
-            Acc o0[RPW], o1[RPW];
-#pragma unroll
-            for (int pb = 0; pb < RPW; ++pb) o0[pb] = o1[pb] = Acc(0);
-#pragma unroll
-            for (int cb = 0; cb < NCB; ++cb)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const Acc w0 = hw0[cb][r], w1 = hw1[cb][r], bc = bpre[cb][r];
-#pragma unroll
-                    for (int pb = 0; pb < RPW; ++pb) {
-                        Acc q = acc[pb][cb][r] + bc;
-                        if (relu) q = q > Acc(0) ? q : Acc(0);
-                        q = P::val(P::cvt(q));
-                        o0[pb] += q * w0;
-                        o1[pb] += q * w1;
-                    }
-                }
-            const double sfac = ex.head_fixed_s > 0 ? ex.head_fixed_s : ex.head_sc[0];
-#pragma unroll
-            for (int pb = 0; pb < RPW; ++pb) {
-                Acc a0 = o0[pb], a1 = o1[pb];
-                a0 += __shfl_xor(a0, 16, 64);
-                a1 += __shfl_xor(a1, 16, 64);
-                a0 += __shfl_xor(a0, 32, 64);
-                a1 += __shfl_xor(a1, 32, 64);
-                const int gy = ty0 + RPW * wv + pb;
-                if (lg == 0 && gy < ex.head_nyt && gx < ex.head_nxt) {
-                    const double2 zv{sfac * (double)(hb0 + a0), sfac * (double)(hb1 + a1)};
-                    const int64_t zi = (int64_t)gy * ex.head_nxt + gx;
-                    if (ex.head_c128) ((double2*)ex.head_z)[zi] = zv;
-                    else ((float2*)ex.head_z)[zi] = from_d2<float2>(zv);
-                }
-            }
-            return;
-        }
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb) {
             const int co = co0 + cb * 16;
@@ -795,16 +756,8 @@ __device__ __forceinline__ void conv3_ws_body(const typename P::T* __restrict__ 
             for (int r = 0; r < 4; ++r) {
                 const int co = co0 + cb * 16 + P::row_of(lg, r);
                 bpre[cb][r] = bias[co];
-                if constexpr (HEAD) {
-                    hw0[cb][r] = P::val(((const T*)ex.head_w)[co]);
-                    hw1[cb][r] = P::val(((const T*)ex.head_w)[cout_p + co]);
-                }
             }
-        if constexpr (HEAD) {
-            hb0 = ((const Acc*)ex.head_b)[0];
-            hb1 = ((const Acc*)ex.head_b)[1];
-        }
-        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): bias (and head) in registers before the loop
+        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): bias in registers before the loop
         for (int t = t_beg; t < t_end; ++t) {
             compute(t, (t - t_beg) & 1);
             __syncthreads();
@@ -834,10 +787,10 @@ __global__ __launch_bounds__(WS_THREADS) void k_conv3_ws(const typename P::T* __
     const int ntiles = ((W + TW - 1) / TW) * ((H + 4 * RPW - 1) / (4 * RPW));
     const int t_beg = grp * tpb, t_end = min(ntiles, t_beg + tpb);
     const int64_t plane = (int64_t)H * W;
-    conv3_ws_body<P, TN, POOL, RPW, WCH, K, false>(
+    conv3_ws_body<P, TN, POOL, RPW, WCH, K>(
         x0 + (int64_t)bz * plane * c0, c0, x1 ? x1 + (int64_t)bz * plane * c1 : nullptr, c1, w, bias,
         y + (int64_t)bz * plane * cout_p, cout_p, POOL ? ypool + (int64_t)bz * (plane / 4) * cout_p : nullptr, H, W,
-        relu, cbi * TN, t_beg, t_end, skipped, Conv3Out());
+        relu, cbi * TN, t_beg, t_end, skipped);
 }
 
 // The same for an input of one k-group per tap (conv3_ws_small): no pooled output.
@@ -861,38 +814,25 @@ __global__ __launch_bounds__(WS_THREADS) void k_conv3_ws8(const typename P::T* _
     const int64_t plane = (int64_t)H * W;
     const typename P::T* xs = x0 + (int64_t)bz * plane * c0;
     // (the second input part is empty; xs stands in for its pointer, which is never read)
-    conv3_ws_body<P, TN, false, RPW, 1, K, false, true>(xs, c0, xs, 0, w, bias,
+    conv3_ws_body<P, TN, false, RPW, 1, K, true>(xs, c0, xs, 0, w, bias,
                                                         y + (int64_t)bz * plane * cout_p, cout_p, nullptr, H, W, relu,
-                                                        cbi * TN, t_beg, t_end, skipped, Conv3Out());
+                                                        cbi * TN, t_beg, t_end, skipped);
 }
 
 // Ragged batch, weight-stationary form: job = (system, first output channel, first tile, end
-// tile) in the fields (sys, c0, ty0, tx0); with HEAD the fused 1x1 head writes column col of the
-// system's z (LayerIO head fields) instead of y.
-template <class P, int TN, bool POOL, int RPW, int WCH, int K, bool HEAD, bool SMALL>
+// tile) in the fields (sys, c0, ty0, tx0).
+template <class P, int TN, bool POOL, int RPW, int WCH, int K, bool SMALL>
 __global__ __launch_bounds__(WS_THREADS) void k_conv3_ws_jobs(const TileJob* __restrict__ jobs,
                                                               const LayerIO* __restrict__ io,
                                                               const typename P::T* __restrict__ w,
                                                               const typename P::Acc* __restrict__ bias, int c0, int c1,
-                                                              int cout_p, const typename P::T* __restrict__ head_w,
-                                                              const typename P::Acc* __restrict__ head_b, int col,
-                                                              int c128) {
+                                                              int cout_p) {
     const TileJob jb = jobs[xcd_linear(blockIdx.x, gridDim.x)];
     const LayerIO d = io[jb.sys];
     if (d.stop && *d.stop) return;
-    Conv3Out ex;
-    if constexpr (HEAD) {
-        ex.head_w = head_w;
-        ex.head_b = head_b;
-        ex.head_c128 = c128;
-        ex.head_z = c128 ? (void*)((double2*)d.z + (int64_t)col * d.zld) : (void*)((float2*)d.z + (int64_t)col * d.zld);
-        ex.head_nxt = d.nxt;
-        ex.head_nyt = d.nyt;
-        ex.head_sc = d.sc;
-    }
-    conv3_ws_body<P, TN, POOL, RPW, WCH, K, HEAD, SMALL>((const typename P::T*)d.x0, c0, (const typename P::T*)d.x1, c1, w,
-                                                  bias, (typename P::T*)d.y, cout_p, (typename P::T*)d.ypool, d.H,
-                                                  d.W, 1, jb.c0, jb.ty0, jb.tx0, 0, ex);
+    conv3_ws_body<P, TN, POOL, RPW, WCH, K, SMALL>((const typename P::T*)d.x0, c0, (const typename P::T*)d.x1, c1, w, bias,
+                                                   (typename P::T*)d.y, cout_p, (typename P::T*)d.ypool, d.H, d.W, 1,
+                                                   jb.c0, jb.ty0, jb.tx0, 0);
 }
 
 // Decoder 3x3 convolution with the transposed convolution of the coarser level fused in (UpIn).
@@ -1363,32 +1303,11 @@ static int check_conv3_extras(int cout_p, bool pool, int batch, const Conv3Out& 
 template <class P>
 static int pick_stream(int c0, int c1, int cout_p, int H, int W, int batch, const Conv3Out& ex, const ConvCfg& cfg) {
     const bool head = ex.head_w != nullptr;
-    if (!conv3s_layer_ok(c0, c1, cout_p)) return 0;
-    auto fits = [&](int id) { return conv3s_form_ok<P>(id, c0, c1, cout_p, ex.split, head); };
-    if (cfg.st > 0 && fits(cfg.st)) return cfg.st;
+    if (cfg.st > 0 && conv3s_form_ok<P>(cfg.st, c0, c1, cout_p, ex.split, head)) return cfg.st;
     if (cfg.tn > 0) return 0;   // a staged form was chosen
-    // The form with the largest tile among those that give the 256 CUs enough blocks: two blocks per
-    // CU of the 64- and 128-channel tiles of 8 rows, four of the 16-row ones; with fewer, the latency
-    // of a block's chunks is in the open and smaller tiles win (256 -> 256 channels at 136^2: 612
-    // blocks of form 7 in 26 us, form 2 27 us; 512 -> 512 at 68^2: 360 blocks of form 7 in 33 us, 680
-    // of form 2 in 28 us; 128 -> 128 at 74^2: 190 blocks of form 2 in 7.0 us, 370 of form 1 in 7.4).
-    // FP32 is bound by the matrix cores: the smaller tiles, which pad ragged images less, win sooner.
-    struct Pick {
-        int id, blocks;
-    };
-    constexpr Pick order_bf16[] = {{4, 512}, {7, 512}, {10, 1024}, {2, 160}, {5, 320}, {1, 0}, {11, 0}, {9, 0}, {12, 0}};
-    constexpr Pick order_f32[] = {{2, 512}, {5, 512}, {11, 0}, {9, 0}, {12, 0}};
-    const bool bf = std::is_same<P, PolBF16>::value;
-    const Pick* order = bf ? order_bf16 : order_f32;
-    const int norder = bf ? (int)(sizeof(order_bf16) / sizeof(Pick)) : (int)(sizeof(order_f32) / sizeof(Pick));
-    for (int i = 0; i < norder; ++i) {
-        const Pick& p = order[i];
-        if (!fits(p.id)) continue;
-        const Conv3sForm f = conv3s_form(p.id);
-        const int64_t nb = (int64_t)((W + 15) / 16) * ((H + f.th() - 1) / f.th()) * (cout_p / f.tn()) * batch;
-        if (nb >= p.blocks) return p.id;
-    }
-    return 0;
+    return conv3s_pick<P>(c0, c1, cout_p, ex.split, head, [&](int th) {
+        return (int64_t)((W + 15) / 16) * ((H + th - 1) / th) * batch;
+    });
 }
 
 template <class P>
@@ -1699,35 +1618,21 @@ int launch_conv3_jobs_head(const TileJob* jobs, int njobs, const LayerIO* io, co
 
 template <class P>
 int launch_conv3_ws_jobs(const TileJob* jobs, int njobs, const LayerIO* io, const typename P::T* w,
-                         const typename P::Acc* bias, int c0, int c1, int cout_p, bool pool,
-                         const typename P::T* head_w, const typename P::Acc* head_b, int col, bool c128,
-                         hipStream_t s) {
+                         const typename P::Acc* bias, int c0, int c1, int cout_p, bool pool, hipStream_t s) {
     if (njobs <= 0) return HZ_OK;
     if constexpr (std::is_same<P, PolBF16>::value) {
         const int nch = (c0 + c1) / P::CK;
-        if (!ws_jobs_ok<P>(c0, c1, cout_p) || (head_w && (pool || cout_p != WSJ_TN))) {
+        const bool small = conv3_ws_small<P>(c0, c1);
+        if (!ws_jobs_ok<P>(c0, c1, cout_p) || (small && pool)) {
             set_error("conv3 jobs: the weight-stationary form needs BF16, 32-channel blocks, 1 or 2 input chunks");
             return HZ_ERR_ARG;
         }
-#define HZ_WSJ(PL, WC, HD, SM)                                                                                  \
-    hipLaunchKernelGGL((k_conv3_ws_jobs<P, WSJ_TN, PL, WSJ_RPW, WC, 2, HD, SM>), dim3(njobs), dim3(WS_THREADS), 0, \
-                       s, jobs, io, w, bias, c0, c1, cout_p, head_w, head_b, col, c128 ? 1 : 0)
-        if (conv3_ws_small<P>(c0, c1)) {
-            if (head_w || pool) {
-                set_error("conv3 jobs: an input of one k-group per tap has no fused head or pooling here");
-                return HZ_ERR_ARG;
-            }
-            HZ_WSJ(false, 1, false, true);
-        } else if (head_w) {
-            if (nch == 1) HZ_WSJ(false, 1, true, false);
-            else HZ_WSJ(false, 2, true, false);
-        } else if (pool) {
-            if (nch == 1) HZ_WSJ(true, 1, false, false);
-            else HZ_WSJ(true, 2, false, false);
-        } else {
-            if (nch == 1) HZ_WSJ(false, 1, false, false);
-            else HZ_WSJ(false, 2, false, false);
-        }
+#define HZ_WSJ(PL, WC, SM)                                                                                          \
+    hipLaunchKernelGGL((k_conv3_ws_jobs<P, WSJ_TN, PL, WSJ_RPW, WC, 2, SM>), dim3(njobs), dim3(WS_THREADS), 0, s, jobs, \
+                       io, w, bias, c0, c1, cout_p)
+        if (small) HZ_WSJ(false, 1, true);
+        else if (nch == 1) { if (pool) HZ_WSJ(true, 1, false); else HZ_WSJ(false, 1, false); }
+        else { if (pool) HZ_WSJ(true, 2, false); else HZ_WSJ(false, 2, false); }
 #undef HZ_WSJ
         HZ_LAUNCH_CHECK();
         return HZ_OK;
@@ -1788,7 +1693,7 @@ int launch_convT2_jobs(const TileJob* jobs, int njobs, const LayerIO* io, const 
     template int launch_conv3_jobs_head<P>(const TileJob*, int, const LayerIO*, const P::T*, const P::Acc*, int,   \
                                            int, int, const P::T*, const P::Acc*, int, bool, hipStream_t);       \
     template int launch_conv3_ws_jobs<P>(const TileJob*, int, const LayerIO*, const P::T*, const P::Acc*, int, int, \
-                                         int, bool, const P::T*, const P::Acc*, int, bool, hipStream_t);        \
+                                         int, bool, hipStream_t);                                               \
     template int launch_convT2_jobs<P>(const TileJob*, int, const LayerIO*, const P::T*, const P::Acc*, int, int, \
                                        int, hipStream_t);                                                      \
     template int launch_convT2_ws_jobs<P>(const TileJob*, int, const LayerIO*, const P::T*, const P::Acc*, int,    \

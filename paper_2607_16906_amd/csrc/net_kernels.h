@@ -234,6 +234,30 @@ constexpr bool conv3s_form_ok(int id, int c0, int c1, int cout_p, int split, boo
     if (cout_p % f.tn() || split % f.tn()) return false;
     return !head || (f.wc == 1 && cout_p == f.tn());
 }
+// Streamed form of a layer with tiles(th) pixel tiles of th x 16 in all (0: it has none). The form
+// with the largest tile among those that give the 256 CUs enough blocks: two blocks per
+// CU of the 64- and 128-channel tiles of 8 rows, four of the 16-row ones; with fewer, the latency
+// of a block's chunks is in the open and smaller tiles win (256 -> 256 channels at 136^2: 612
+// blocks of form 7 in 26 us, form 2 27 us; 512 -> 512 at 68^2: 360 blocks of form 7 in 33 us, 680
+// of form 2 in 28 us; 128 -> 128 at 74^2: 190 blocks of form 2 in 7.0 us, 370 of form 1 in 7.4).
+// FP32 is bound by the matrix cores: the smaller tiles, which pad ragged images less, win sooner.
+template <class P, typename F>
+int conv3s_pick(int c0, int c1, int cout_p, int split, bool head, F tiles) {
+    struct Pick {
+        int id, blocks;
+    };
+    constexpr Pick order_bf16[] = {{4, 512}, {7, 512}, {10, 1024}, {2, 160}, {5, 320}, {1, 0}, {11, 0}, {9, 0}, {12, 0}};
+    constexpr Pick order_f32[] = {{2, 512}, {5, 512}, {11, 0}, {9, 0}, {12, 0}};
+    const bool bf = std::is_same<P, PolBF16>::value;
+    const Pick* order = bf ? order_bf16 : order_f32;
+    const int norder = bf ? (int)(sizeof(order_bf16) / sizeof(Pick)) : (int)(sizeof(order_f32) / sizeof(Pick));
+    for (int i = 0; i < norder; ++i) {
+        if (!conv3s_form_ok<P>(order[i].id, c0, c1, cout_p, split, head)) continue;
+        const Conv3sForm f = conv3s_form(order[i].id);
+        if (tiles(f.th()) * (cout_p / f.tn()) >= order[i].blocks) return order[i].id;
+    }
+    return 0;
+}
 // Position of weight (tap, co, ci) in a streamed pack of T: operands of 1 KB [chunk][channel block][tap],
 // 16 bytes per lane (row co % 16, lane group lg). BF16: chunks of 32, lane group lg holds channels
 // 8 lg ..; FP32: chunks of 16, it holds channels lg, 4 + lg, 8 + lg, 12 + lg.
@@ -262,6 +286,12 @@ struct Conv3sArgs {
 };
 template <class P>
 int launch_conv3s(int form, const Conv3sArgs<P>& g, hipStream_t s);
+// The same over a job table of a ragged batch: job = (sys, first output channel, tile row, tile column)
+// with tiles of the form's th() rows x 16; head_w: the fused 1x1 head as in launch_conv3_jobs_head.
+template <class P>
+int launch_conv3s_jobs(int form, const TileJob* jobs, int njobs, const LayerIO* io, const void* wf,
+                       const typename P::Acc* bias, int c0, int c1, int cout_p, bool pool,
+                       const typename P::T* head_w, const typename P::Acc* head_b, int col, bool c128, hipStream_t s);
 
 // Consecutive workgroups are dispatched round-robin over the 8 XCDs, each with its own L2.
 // Renumber the physical block id so that the blocks one XCD runs form one contiguous range of
@@ -294,7 +324,7 @@ int launch_conv3_jobs_head(const TileJob* jobs, int njobs, const LayerIO* io, co
                            const typename P::Acc* head_b, int col, bool c128, hipStream_t s);
 // Weight-stationary form over a job table (BF16, inputs of one or two chunks or of one k-group per
 // tap; WSJ_TN output channels and 4 WSJ_RPW pixel rows per tile; job = (sys, first output channel, first tile, end tile) with tiles row-major over the
-// system's image); with head_w the fused 1x1 head as in launch_conv3_jobs_head (cout_p == WSJ_TN).
+// system's image).
 constexpr int WSJ_TN = 32, WSJ_RPW = 4;
 template <class P>
 constexpr bool ws_jobs_ok(int c0, int c1, int cout_p) {
@@ -302,9 +332,7 @@ constexpr bool ws_jobs_ok(int c0, int c1, int cout_p) {
 }
 template <class P>
 int launch_conv3_ws_jobs(const TileJob* jobs, int njobs, const LayerIO* io, const typename P::T* w,
-                         const typename P::Acc* bias, int c0, int c1, int cout_p, bool pool,
-                         const typename P::T* head_w, const typename P::Acc* head_b, int col, bool c128,
-                         hipStream_t s);
+                         const typename P::Acc* bias, int c0, int c1, int cout_p, bool pool, hipStream_t s);
 template <class P>
 int launch_convT2_jobs(const TileJob* jobs, int njobs, const LayerIO* io, const typename P::T* w,
                        const typename P::Acc* bias, int cin_p, int cout_p, int tn, hipStream_t s);

@@ -320,4 +320,29 @@ __global__ __launch_bounds__(64 * WC * WR, 2) void k_conv3s(
                                           cbi * TN, tyi * TH, txi * 16, skipped);
 }
 
+// Ragged batch: block b runs job jobs[b] with the system's tensors; with the fused head, column col
+// of the system's z.
+template <class S, int NCB, int RPW, int WC, int WR, int EPI>
+__global__ __launch_bounds__(64 * WC * WR, 2) void k_conv3s_jobs(
+    const TileJob* __restrict__ jobs, const LayerIO* __restrict__ io, const void* __restrict__ wf,
+    const float* __restrict__ bias, int c0, int c1, int cout_p, const typename S::P::T* __restrict__ head_w,
+    const float* __restrict__ head_b, int col, int c128) {
+    using T = typename S::P::T;
+    const TileJob jb = jobs[xcd_linear(blockIdx.x, gridDim.x)];
+    const LayerIO d = io[jb.sys];
+    if (d.stop && *d.stop) return;
+    Conv3Out ex;
+    if constexpr (EPI == CS_HEAD) {
+        ex.head_w = head_w;
+        ex.head_b = head_b;
+        ex.head_c128 = c128;
+        ex.head_z = c128 ? (void*)((double2*)d.z + (int64_t)col * d.zld) : (void*)((float2*)d.z + (int64_t)col * d.zld);
+        ex.head_nxt = d.nxt;
+        ex.head_nyt = d.nyt;
+        ex.head_sc = d.sc;
+    }
+    conv3s_tile<S, NCB, RPW, WC, WR, EPI>((const T*)d.x0, c0, (const T*)d.x1, c1, wf, bias, (T*)d.y, cout_p,
+                                          (T*)d.ypool, d.H, d.W, 1, ex, jb.c0, jb.ty0, jb.tx0, 0);
+}
+
 }  // namespace hz

@@ -47,4 +47,47 @@ static int launch_conv3s_any(int form, const Conv3sArgs<typename S::P>& g, hipSt
     return HZ_ERR_ARG;
 }
 
+template <class S, int NCB, int RPW, int WC, int WR>
+static int launch_form_jobs(const TileJob* jobs, int njobs, const LayerIO* io, const void* wf, const float* bias, int c0,
+                            int c1, int cout_p, bool pool, const typename S::P::T* head_w, const float* head_b, int col,
+                            bool c128, hipStream_t s) {
+#define HZ_CSJ(E)                                                                                                    \
+    hipLaunchKernelGGL((k_conv3s_jobs<S, NCB, RPW, WC, WR, E>), dim3(njobs), dim3(64 * WC * WR), 0, s, jobs, io, wf, bias, \
+                       c0, c1, cout_p, head_w, head_b, col, c128 ? 1 : 0)
+    if (head_w) {
+        if constexpr (WC == 1) HZ_CSJ(CS_HEAD);
+    } else if (pool) {
+        HZ_CSJ(CS_POOL);
+    } else {
+        HZ_CSJ(CS_PLAIN);
+    }
+#undef HZ_CSJ
+    HZ_LAUNCH_CHECK();
+    return HZ_OK;
+}
+
+template <class S>
+static int launch_conv3s_jobs_any(int form, const TileJob* jobs, int njobs, const LayerIO* io, const void* wf,
+                                  const float* bias, int c0, int c1, int cout_p, bool pool,
+                                  const typename S::P::T* head_w, const float* head_b, int col, bool c128,
+                                  hipStream_t s) {
+    if (njobs <= 0) return HZ_OK;
+    if (!conv3s_form_ok<typename S::P>(form, c0, c1, cout_p, 0, head_w != nullptr) || !wf || (head_w && pool)) {
+        set_error("conv3 jobs: the streamed form does not take these channels");
+        return HZ_ERR_ARG;
+    }
+    switch (form) {   // the forms conv3s_pick chooses from
+#define HZ_CSF(ID, NCB, RPW, WC, WR)                                                                              \
+    case ID:                                                                                                      \
+        if constexpr (ID != 3 && ID != 6 && ID != 8 && ID != 13)                                                  \
+            return launch_form_jobs<S, NCB, RPW, WC, WR>(jobs, njobs, io, wf, bias, c0, c1, cout_p, pool, head_w, \
+                                                         head_b, col, c128, s);                                  \
+        else break;
+        HZ_CONV3S_FORMS(HZ_CSF)
+#undef HZ_CSF
+    }
+    set_error("conv3 jobs: unknown streamed form");
+    return HZ_ERR_ARG;
+}
+
 }  // namespace hz
