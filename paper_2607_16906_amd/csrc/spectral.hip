@@ -60,17 +60,25 @@ __global__ void k_spec_mmat(double2* __restrict__ Md, float2* __restrict__ Mf, c
     Mf[(int64_t)j * n + l] = float2{(float)m.x, (float)m.y};
 }
 
-// Matrix-core form. The two per-axis contractions are complex GEMMs, each taken as four real
-// 16 x 16 x 4 MFMA products per k-step (re += a.re b.re - a.im b.im, im += a.re b.im + a.im b.re,
-// the negated a.im staged beside a.im). A block of 8 wavefronts owns a 32 x 32 output tile:
-// wavefronts 0-3 form the x part sum_k u[y][k] Mx'[x][k] of one 16 x 16 quarter each, wavefronts
-// 4-7 the y part sum_k My'[y][k] u[k][x] of the same quarters, both over chunks of SPK k values
-// staged together in LDS (the next chunk's values in registers meanwhile). The y part is then
-// added to the x part (in that order) and the epilogue adds k^2 u; for RESID it forms
-// r = b - A u with the tile's ||r||^2 in part[tile]. Mx' = Mx and My' = My, or for ADJ
-// Mx'[x][k] = conj(Mx[k][x]) and My'[y][k] = conj(My[k][y]). FP32 takes v_mfma_f32_16x16x4_f32,
-// FP64 v_mfma_f64_16x16x4_f64.
-constexpr int SPT = 32;     // output tile edge
+// Matrix-core form. The two per-axis contractions are complex GEMMs, each taken as three real
+// 16 x 16 x 4 MFMA products per k-step (s1 += (a.re + a.im) b.re, s2 += a.re (b.im - b.re), s3 += a.im
+// (b.re + b.im); re = s1 - s3, im = s1 + s2).
+// A block of 8 wavefronts owns a (16 NB) x (16 NB) output tile; wavefronts 0-3 form the x part sum_k
+// u[y][k] Mx'[x][k], wavefronts 4-7 the y part sum_k My'[y][k] u[k][x], each over every fourth chunk
+// of SPK k values. Operands go from memory straight into registers, the next chunk's while the matrix
+// cores work: lane group g holds k values 4 g .. 4 g + 3 of a chunk and step s contracts the s-th of
+// each group (the order of the contraction is free as long as both operands agree), so a lane reads
+// 4 consecutive complex values of a row. The 8 partial tiles meet in LDS and are added in wavefront
+// order; the epilogue adds k^2 u, and for RESID forms r = b - A u with the tile's ||r||^2 in
+// part[tile]. Mx' = Mx and My' = My, or for ADJ Mx'[x][k] = conj(Mx[k][x]) and My'[y][k] =
+// conj(My[k][y]). FP32 takes v_mfma_f32_16x16x4_f32, FP64 v_mfma_f64_16x16x4_f64.
+//
+// 32 x 32 tiles are bound by the matrix cores (48 instructions per 4 operands of 16 k values); at small
+// grids the chain of a block's chunks takes the time, which 16 x 16 tiles with a quarter of the chunks
+// per wavefront shorten. Measured against 32 x 32 tiles staged in LDS, with four products per complex
+// product and one chain per part: 296^2 20.4 -> 10 us FP32, 30 -> 19 us FP64; 1088^2 234 -> 178 us FP32 (117
+// of 157 TFLOP/s, counting four products), 376 -> 365 us FP64. The error against 64 bits falls, too
+// (FP32, 1088^2: 7.1e-7 -> 4.0e-7), from the shorter sums.
 constexpr int SPK = 16;     // k values per chunk
 constexpr int SPW = 512;    // threads per block
 
@@ -89,7 +97,23 @@ struct SpecMma<double> {
     __device__ static int row_of(int lg, int r) { return lg + 4 * r; }
 };
 
-template <typename C, bool ADJ, bool RESID>
+// 4 consecutive complex values of a row (FP32: 8-byte aligned, an odd row length leaves no more)
+template <typename C>
+__device__ __forceinline__ void load_row4(const C* p, C (&v)[4]) {
+    if constexpr (sizeof(C) == 8) {
+        typedef float f4_t __attribute__((ext_vector_type(4), aligned(8)));
+        const f4_t a = *(const f4_t*)p, b = *(const f4_t*)(p + 2);
+        v[0] = C{a.x, a.y};
+        v[1] = C{a.z, a.w};
+        v[2] = C{b.x, b.y};
+        v[3] = C{b.z, b.w};
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = p[i];
+    }
+}
+
+template <typename C, bool ADJ, bool RESID, int NB>
 __global__ __launch_bounds__(SPW) void k_spectral(const C* __restrict__ u, C* __restrict__ y, const C* __restrict__ b,
                                                   const C* __restrict__ Mx, const C* __restrict__ My,
                                                   const decltype(C{}.x)* __restrict__ k2, int nx, int ny,
@@ -98,150 +122,182 @@ __global__ __launch_bounds__(SPW) void k_spectral(const C* __restrict__ u, C* __
     using M = SpecMma<T>;
     using V = typename M::V;
     if (skip && *skip) return;
-    // [row][k] operands (u rows for x, My' rows for y) and [k][col] operands (Mx' for x, u for y),
-    // as real and imaginary planes, one padding element per row
-    __shared__ T sa[2][2][SPT][SPK + 1];   // [part][re/im][row][k]
-    __shared__ T sb[2][2][SPK][SPT + 1];   // [part][re/im][k][col]
-    __shared__ V sy[4][2][64];            // y-part accumulators handed to the x-part wavefronts
+    __shared__ T red[8][2][NB][256];      // one row of 16 x 16 blocks at a time: [wavefront][re/im][block][entry]
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int prt = wv >> 2;              // 0: x part, 1: y part
-    const int q = wv & 3;                 // output quarter: rows 16 (q / 2), columns 16 (q % 2)
+    // x / y part, every fourth chunk from kq on (shifted between the parts, so that the two wavefronts
+    // of a SIMD do not both have the longer share)
+    const int prt = wv >> 2, kq = (wv + 2 * prt) & 3;
     const int lr = lane & 15, lg = lane >> 4;
-    const int x0 = blockIdx.x * SPT, y0 = blockIdx.y * SPT;
-    const int nch = (max(nx, ny) + SPK - 1) / SPK;
-    // staging: each thread moves one [row][k] and one [k][col] element of each part per chunk
-    // (1024 + 1024 elements, 512 threads, two of each kind per thread)
-    C ra[2][2], rb[2][2];
-    auto gload = [&](int ch) {
-        const int k0 = ch * SPK;
+    const int x0 = blockIdx.x * 16 * NB, y0 = blockIdx.y * 16 * NB;
+    const int nk = prt ? ny : nx;
+    // rows and columns past the grid repeat the last one; their entries are not written
+    int gy[NB], gx[NB];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int e = threadIdx.x + SPW * i;          // 0 .. 1023
-            const int pp = e >> 9, f = e & 511;           // part, element of the 32 x 16 / 16 x 32 tile
-            if (pp == 0) {
-                // x part: a = u[y0 + r][k0 + kk] (k fastest); b = Mx'[x0 + c][k0 + kk]
-                const int r = f / SPK, kk = f % SPK;
-                const int gy = y0 + r, gk = k0 + kk;
-                ra[i][0] = (gy < ny && gk < nx) ? u[(int64_t)gy * nx + gk] : C{0, 0};
-                if (ADJ) {   // conj(Mx[k][x]): x fastest
-                    const int kr = f / SPT, c = f % SPT;
-                    const int gx = x0 + c, gk2 = k0 + kr;
-                    const C v = (gx < nx && gk2 < nx) ? Mx[(int64_t)gk2 * nx + gx] : C{0, 0};
-                    rb[i][0] = C{v.x, -v.y};
-                } else {     // Mx[x][k]: k fastest
-                    const int c = f / SPK, kk2 = f % SPK;
-                    const int gx = x0 + c, gk2 = k0 + kk2;
-                    rb[i][0] = (gx < nx && gk2 < nx) ? Mx[(int64_t)gx * nx + gk2] : C{0, 0};
+    for (int i = 0; i < NB; ++i) gy[i] = min(y0 + 16 * i + lr, ny - 1);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) gx[i] = min(x0 + 16 * i + lr, nx - 1);
+    // operands of the chunk whose k values of this lane start at k: a[i] rows y0 + 16 i.., b[i] columns
+    auto gload = [&](int k, bool whole, C (&a)[NB][4], C (&bb)[NB][4]) {
+        if (whole) {
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                if (prt == 0) load_row4(u + (int64_t)gy[i] * nx + k, a[i]);
+                else if (!ADJ) load_row4(My + (int64_t)gy[i] * ny + k, a[i]);
+                else {
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) a[i][s] = My[(int64_t)(k + s) * ny + gy[i]];
                 }
-            } else {
-                // y part: a = My'[y0 + r][k0 + kk]; b = u[k0 + kk][x0 + c] (x fastest)
-                if (ADJ) {   // conj(My[k][y]): y fastest
-                    const int kk = f / SPT, r = f % SPT;
-                    const int gy = y0 + r, gk = k0 + kk;
-                    const C v = (gy < ny && gk < ny) ? My[(int64_t)gk * ny + gy] : C{0, 0};
-                    ra[i][1] = C{v.x, -v.y};
-                } else {     // My[y][k]: k fastest
-                    const int r = f / SPK, kk = f % SPK;
-                    const int gy = y0 + r, gk = k0 + kk;
-                    ra[i][1] = (gy < ny && gk < ny) ? My[(int64_t)gy * ny + gk] : C{0, 0};
+            }
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                if (prt == 0 && !ADJ) load_row4(Mx + (int64_t)gx[i] * nx + k, bb[i]);
+                else {
+                    const C* src = prt == 0 ? Mx : u;
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) bb[i][s] = src[(int64_t)(k + s) * nx + gx[i]];
                 }
-                const int kr = f / SPT, c = f % SPT;
-                const int gk2 = k0 + kr, gx = x0 + c;
-                rb[i][1] = (gk2 < ny && gx < nx) ? u[(int64_t)gk2 * nx + gx] : C{0, 0};
+            }
+            return;
+        }
+        // the last chunk of a ragged length: zeros past its end
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const int kl = k + s;
+            const bool in = kl < nk;
+            const int kk = in ? kl : 0;
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                const C v = prt == 0 ? u[(int64_t)gy[i] * nx + kk]
+                                     : (ADJ ? My[(int64_t)kk * ny + gy[i]] : My[(int64_t)gy[i] * ny + kk]);
+                a[i][s] = in ? v : C{0, 0};
+            }
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                const C v = prt == 0 ? (ADJ ? Mx[(int64_t)kk * nx + gx[i]] : Mx[(int64_t)gx[i] * nx + kk])
+                                     : u[(int64_t)kk * nx + gx[i]];
+                bb[i][s] = in ? v : C{0, 0};
             }
         }
     };
-    auto lstore = [&]() {
+    V s1[NB][NB], s2[NB][NB], s3[NB][NB];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int e = threadIdx.x + SPW * i;
-            const int pp = e >> 9, f = e & 511;
-            if (pp == 0) {
-                const int r = f / SPK, kk = f % SPK;
-                sa[0][0][r][kk] = ra[i][0].x;
-                sa[0][1][r][kk] = ra[i][0].y;
-                int kr, c;
-                if (ADJ) { kr = f / SPT; c = f % SPT; } else { c = f / SPK; kr = f % SPK; }
-                sb[0][0][kr][c] = rb[i][0].x;
-                sb[0][1][kr][c] = rb[i][0].y;
-            } else {
-                int r, kk;
-                if (ADJ) { kk = f / SPT; r = f % SPT; } else { r = f / SPK; kk = f % SPK; }
-                sa[1][0][r][kk] = ra[i][1].x;
-                sa[1][1][r][kk] = ra[i][1].y;
-                const int kr = f / SPT, c = f % SPT;
-                sb[1][0][kr][c] = rb[i][1].x;
-                sb[1][1][kr][c] = rb[i][1].y;
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) s1[i][j][r] = s2[i][j][r] = s3[i][j][r] = T(0);
+    const int nch = (nk + SPK - 1) / SPK;
+    // two operand sets in turn: one is loaded while the matrix cores work on the other
+    C a0[NB][4], b0[NB][4], a1[NB][4], b1[NB][4];
+    auto at = [&](int ch, C (&a)[NB][4], C (&bb)[NB][4]) {
+        if (ch < nch) gload(ch * SPK + 4 * lg, (ch + 1) * SPK <= nk, a, bb);
+    };
+    auto compute = [&](C (&a)[NB][4], C (&bb)[NB][4]) {
+        // (the conjugated matrix: My' is the first operand of the y part, Mx' the second of the x part)
+        if (ADJ) {
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    a[i][s].y = prt == 1 ? -a[i][s].y : a[i][s].y;
+                    bb[i][s].y = prt == 0 ? -bb[i][s].y : bb[i][s].y;
+                }
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            T as[NB], bd[NB], bs[NB];
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                as[i] = a[i][s].x + a[i][s].y;
+                bd[i] = bb[i][s].y - bb[i][s].x;
+                bs[i] = bb[i][s].x + bb[i][s].y;
             }
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+#pragma unroll
+                for (int j = 0; j < NB; ++j) {
+                    s1[i][j] = M::mma(as[i], bb[j][s].x, s1[i][j]);
+                    s2[i][j] = M::mma(a[i][s].x, bd[j], s2[i][j]);
+                    s3[i][j] = M::mma(a[i][s].y, bs[j], s3[i][j]);
+                }
         }
     };
-    V are, aim;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) are[r] = aim[r] = T(0);
-    const int ar0 = 16 * (q >> 1), bc0 = 16 * (q & 1);
-    gload(0);
-    for (int ch = 0; ch < nch; ++ch) {
-        __syncthreads();
-        lstore();
-        __syncthreads();
-        if (ch + 1 < nch) gload(ch + 1);
-#pragma unroll
-        for (int st = 0; st < SPK / 4; ++st) {
-            const int kk = 4 * st + lg;
-            const T a_re = sa[prt][0][ar0 + lr][kk], a_im = sa[prt][1][ar0 + lr][kk];
-            const T b_re = sb[prt][0][kk][bc0 + lr], b_im = sb[prt][1][kk][bc0 + lr];
-            are = M::mma(a_re, b_re, are);
-            are = M::mma(-a_im, b_im, are);
-            aim = M::mma(a_re, b_im, aim);
-            aim = M::mma(a_im, b_re, aim);
+    at(kq, a0, b0);
+    for (int ch = kq; ch < nch; ch += 8) {
+        at(ch + 4, a1, b1);
+        compute(a0, b0);
+        if (ch + 4 < nch) {
+            at(ch + 8, a0, b0);
+            compute(a1, b1);
         }
     }
-    // y part into LDS, then the x-part wavefronts add it and finish
-    if (prt == 1) {
-        sy[q][0][lane] = are;
-        sy[q][1][lane] = aim;
-    }
-    __syncthreads();
+    // add the 8 partial tiles, one row of 16 x 16 blocks at a time: thread t finishes entry t % 256 (row
+    // t / 16 % 16, column t % 16) of block t / 256
     double nrm = 0.0;
-    if (prt == 0) {
-        const V yre = sy[q][0][lane], yim = sy[q][1][lane];
-        const int gx = x0 + bc0 + lr;
+    const int j = threadIdx.x >> 8, e = threadIdx.x & 255;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int gy = y0 + ar0 + M::row_of(lg, r);
-            if (gy < ny && gx < nx) {
-                const int64_t idx = (int64_t)gy * nx + gx;
-                const C uq = u[idx];
-                const T kq = k2[idx];
-                T vr = (are[r] + yre[r]) + kq * uq.x, vi = (aim[r] + yim[r]) + kq * uq.y;
-                if (RESID) {
-                    vr = b[idx].x - vr;
-                    vi = b[idx].y - vi;
-                    nrm += (double)vr * vr + (double)vi * vi;
-                }
-                y[idx] = C{vr, vi};
+    for (int i = 0; i < NB; ++i) {
+        if (i) __syncthreads();
+#pragma unroll
+        for (int jj = 0; jj < NB; ++jj)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int pos = M::row_of(lg, r) * 16 + lr;
+                red[wv][0][jj][pos] = s1[i][jj][r] - s3[i][jj][r];
+                red[wv][1][jj][pos] = s1[i][jj][r] + s2[i][jj][r];
             }
+        __syncthreads();
+        const int oy = y0 + 16 * i + (e >> 4), ox = x0 + 16 * j + (e & 15);
+        if (j < NB && oy < ny && ox < nx) {
+            T vr = red[0][0][j][e], vi = red[0][1][j][e];
+#pragma unroll
+            for (int w = 1; w < 8; ++w) {
+                vr += red[w][0][j][e];
+                vi += red[w][1][j][e];
+            }
+            const int64_t idx = (int64_t)oy * nx + ox;
+            const C uq = u[idx];
+            const T kq2 = k2[idx];
+            vr += kq2 * uq.x;
+            vi += kq2 * uq.y;
+            if (RESID) {
+                vr = b[idx].x - vr;
+                vi = b[idx].y - vi;
+                nrm += (double)vr * vr + (double)vi * vi;
+            }
+            y[idx] = C{vr, vi};
         }
     }
     if (RESID) {
-        __shared__ double red[SPW / 64];
-        double t = nrm;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
-        if (lane == 0) red[wv] = t;
+        __shared__ double rn[SPW / 64];
+        const double t = wave_sum(nrm);
+        if (lane == 0) rn[wv] = t;
         __syncthreads();
         if (threadIdx.x == 0) {
             double acc = 0.0;
 #pragma unroll
-            for (int w = 0; w < 4; ++w) acc += red[w];   // the x-part wavefronts hold the values
+            for (int w = 0; w < SPW / 64; ++w) acc += rn[w];
             part[blockIdx.y * gridDim.x + blockIdx.x] = acc;
         }
     }
 }
 
+// Edge of a grid's tiles in 16 x 16 blocks: 2 or 1. A CU runs one block at a time, so a launch takes
+// its tiles in rounds of 256; a small tile takes about 6/5 of a quarter of a large one's time (fewer
+// matrix instructions per load): 544^2, 289 large tiles in two rounds 48 us, 1156 small ones in five
+// 38 us; 488^2, 256 large ones in one round 25 us, 961 small ones 26 us (FP32).
+static int spectral_nb(const hz_problem* p) {
+    auto rounds = [&](int te) {
+        const int64_t t = (int64_t)((p->nxt + te - 1) / te) * ((p->nyt + te - 1) / te);
+        return (t + 255) / 256;
+    };
+    return rounds(32) * 4 * 5 <= rounds(16) * 6 ? 2 : 1;
+}
+
 static dim3 spectral_grid(const hz_problem* p) {
-    return dim3((p->nxt + SPT - 1) / SPT, (p->nyt + SPT - 1) / SPT);
+    const int te = 16 * spectral_nb(p);
+    return dim3((p->nxt + te - 1) / te, (p->nyt + te - 1) / te);
 }
 
 int spectral_blocks(const hz_problem* p) {
@@ -261,38 +317,42 @@ int spectral_setup(hz_problem* p, hipStream_t s) {
     return HZ_OK;
 }
 
-int launch_spectral(const hz_problem* p, bool fp64, bool adjoint, const void* x, void* y, hipStream_t s,
-                    const int* skip) {
-    const dim3 grid = spectral_grid(p);
-#define HZ_SP(C, A, MX, MY, K2)                                                                                  \
-    hipLaunchKernelGGL((k_spectral<C, A, false>), grid, dim3(SPW), 0, s, (const C*)x, (C*)y, (const C*)nullptr, \
-                       (const C*)MX, (const C*)MY, K2, p->nxt, p->nyt, (double*)nullptr, skip)
-    if (fp64) {
-        if (adjoint) HZ_SP(double2, true, p->Mx_d, p->My_d, p->k2d);
-        else HZ_SP(double2, false, p->Mx_d, p->My_d, p->k2d);
-    } else {
-        if (adjoint) HZ_SP(float2, true, p->Mx_f, p->My_f, p->k2f);
-        else HZ_SP(float2, false, p->Mx_f, p->My_f, p->k2f);
-    }
+template <typename C, bool ADJ, bool RESID>
+static int launch_tile(const hz_problem* p, const C* x, C* y, const C* b, const C* Mx, const C* My,
+                       const decltype(C{}.x)* k2, double* part, const int* skip, hipStream_t s) {
+    const dim3 g = spectral_grid(p);
+#define HZ_SP(NB)                                                                                                  \
+    hipLaunchKernelGGL((k_spectral<C, ADJ, RESID, NB>), g, dim3(SPW), 0, s, x, y, b, Mx, My, k2, p->nxt, p->nyt, \
+                       part, skip)
+    if (spectral_nb(p) == 2) HZ_SP(2);
+    else HZ_SP(1);
 #undef HZ_SP
     HZ_LAUNCH_CHECK();
     return HZ_OK;
 }
 
+int launch_spectral(const hz_problem* p, bool fp64, bool adjoint, const void* x, void* y, hipStream_t s,
+                    const int* skip) {
+    if (fp64) {
+        const double2 *xd = (const double2*)x, *Mx = (const double2*)p->Mx_d, *My = (const double2*)p->My_d;
+        return adjoint ? launch_tile<double2, true, false>(p, xd, (double2*)y, nullptr, Mx, My, p->k2d, nullptr, skip, s)
+                       : launch_tile<double2, false, false>(p, xd, (double2*)y, nullptr, Mx, My, p->k2d, nullptr, skip, s);
+    }
+    const float2 *xf = (const float2*)x, *Mx = (const float2*)p->Mx_f, *My = (const float2*)p->My_f;
+    return adjoint ? launch_tile<float2, true, false>(p, xf, (float2*)y, nullptr, Mx, My, p->k2f, nullptr, skip, s)
+                   : launch_tile<float2, false, false>(p, xf, (float2*)y, nullptr, Mx, My, p->k2f, nullptr, skip, s);
+}
+
 int launch_spectral_resid32(const hz_problem* p, const float2* b, const float2* x, float2* r, double* part,
                             const int* skip, hipStream_t s) {
-    hipLaunchKernelGGL((k_spectral<float2, false, true>), spectral_grid(p), dim3(SPW), 0, s, x, r, b,
-                       (const float2*)p->Mx_f, (const float2*)p->My_f, p->k2f, p->nxt, p->nyt, part, skip);
-    HZ_LAUNCH_CHECK();
-    return HZ_OK;
+    return launch_tile<float2, false, true>(p, x, r, b, (const float2*)p->Mx_f, (const float2*)p->My_f, p->k2f, part,
+                                            skip, s);
 }
 
 int launch_spectral_resid64(const hz_problem* p, const double2* b, const double2* x, double2* r, double* part,
                             const int* skip, hipStream_t s) {
-    hipLaunchKernelGGL((k_spectral<double2, false, true>), spectral_grid(p), dim3(SPW), 0, s, x, r, b,
-                       (const double2*)p->Mx_d, (const double2*)p->My_d, p->k2d, p->nxt, p->nyt, part, skip);
-    HZ_LAUNCH_CHECK();
-    return HZ_OK;
+    return launch_tile<double2, false, true>(p, x, r, b, (const double2*)p->Mx_d, (const double2*)p->My_d, p->k2d, part,
+                                             skip, s);
 }
 
 }  // namespace hz
