@@ -294,7 +294,9 @@ static int64_t layer_jobs_cap(const no_net* net, const std::vector<SysLayout>& S
     int64_t tiles = 0;
     for (const SysLayout& sl : S) {
         const int H = sl.Hp >> level, W = sl.Wp >> level;
-        tiles += convT ? (int64_t)H * ((W + 63) / 64) : (int64_t)((W + 15) / 16) * ((H + 7) / 8);
+        // (transposed layers: row segments of 64 pixels, or 32 pixels of the whole system at least)
+        tiles += convT ? std::max((int64_t)H * ((W + 63) / 64), ((int64_t)H * W + 31) / 32)
+                       : (int64_t)((W + 15) / 16) * ((H + 7) / 8);
     }
     return tiles * (ly.cout_p / 16);
 }
@@ -510,15 +512,20 @@ static void build_tables(const BatchPlan<P>& B, const no_net* net, const std::ve
         const bool fhead = li == nl - 2 && head_fused(net);
         int tn = 16, rpw = 2, tpb = 0, st = 0;
         if (convT) {
+            int64_t npix = 0;
+            for (int s : active) npix += (int64_t)(B.S[s].Hp >> l) * (B.S[s].Wp >> l);
+            if (streamed_w<P>(net, ly)) st = convT2s_pick<P>(ly.cin_p, ly.cout_p, false, npix);
             tn = convT2_batch_tn(ly.cout_p);
+            // (the rule of launch_convT2)
             // weight-stationary form where the input channels fit one stage: 4-32 row segments per
             // job, while that still gives at least 256 jobs
-            if (convT2_ws_ok<P>(ly.cin_p, ly.cout_p, tn)) {
+            if ((!st || ly.cin_p <= 64) && convT2_ws_ok<P>(ly.cin_p, ly.cout_p, tn)) {
                 const int64_t ncb = ly.cout_p / tn;
                 int t = 32;
                 while (t > 4 && (tiles + t - 1) / t * ncb < 1024) t /= 2;
                 if ((tiles + t - 1) / t * ncb >= 256) tpb = t;
             }
+            if (tpb > 0) st = 0;
         } else {
             const int c1 = ly.cat_cp ? ly.cin_p - ly.cat_cp : 0;
             if (streamed_w<P>(net, ly))
@@ -535,7 +542,7 @@ static void build_tables(const BatchPlan<P>& B, const no_net* net, const std::ve
         h.rpw[li] = rpw;
         h.ws[li] = tpb > 0;
         h.st[li] = st;
-        const int th = st ? conv3s_form(st).th() : 4 * rpw;   // tile rows of a 3x3 layer
+        const int th = st && !convT ? conv3s_form(st).th() : 4 * rpw;   // tile rows of a 3x3 layer
         for (int s = 0; s < nsys; ++s) {
             const FwdBufs& fb = B.S[s].fb;
             LayerIO& io = h.io[li][s];
@@ -565,7 +572,11 @@ static void build_tables(const BatchPlan<P>& B, const no_net* net, const std::ve
         // to a contiguous range of jobs, so they share the tile's input in one L2)
         for (int s : active) {
             const int H = B.S[s].Hp >> l, W = B.S[s].Wp >> l;
-            if (convT && tpb > 0) {   // (sys, first channel, first segment, end segment)
+            if (convT && st) {   // (sys, M group, pixel tile)
+                const ConvT2sForm f = convT2s_form(st);
+                for (int t = 0; t < (H * W + f.px - 1) / f.px; ++t)
+                    for (int gm = 0; gm < ly.cout_p / 4 / f.mblk; ++gm) h.cjobs[li].push_back(TileJob{s, gm, t, 0});
+            } else if (convT && tpb > 0) {   // (sys, first channel, first segment, end segment)
                 const int nt = H * ((W + 63) / 64);
                 for (int t0 = 0; t0 < nt; t0 += tpb)
                     for (int co = 0; co < ly.cout_p; co += tn)
@@ -626,7 +637,19 @@ static int net_step(const BatchPlan<P>& B, const HostTables<P>& h, const no_net*
         const Layer& ly = net->layers[li];
         const int nj = (int)h.cjobs[li].size();
         const bool hd = fhead && li == nl - 2;
-        if (role[li] == 2 && h.ws[li]) {
+        if (role[li] == 2 && h.st[li]) {
+            if constexpr (!std::is_same<P, PolF64>::value) {
+                ConvT2sArgs<P> g{};
+                g.KC = ly.cin_p;
+                g.wf = streamed_w<P>(net, ly);
+                g.bias = packed_b<P>(net, ly);
+                g.MC = ly.cout_p;
+                g.jobs = t.cjobs[li];
+                g.njobs = nj;
+                g.io = t.io[li];
+                HZ_TRY(launch_convT2s<P>(h.st[li], g, false, s));
+            }
+        } else if (role[li] == 2 && h.ws[li]) {
             HZ_TRY(launch_convT2_ws_jobs<P>(t.cjobs[li], nj, t.io[li], packed_w<P>(net, ly), packed_b<P>(net, ly),
                                             ly.cin_p, ly.cout_p, h.tn[li], s));
         } else if (h.ws[li]) {

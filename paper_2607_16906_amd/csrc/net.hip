@@ -142,6 +142,16 @@ __global__ void k_repack(const float* __restrict__ theta, const Layer* __restric
             tf[ly.pk_off + j] = v;
             td[ly.pk_off + j] = (double)v;
         }
+        if (ly.kind == L_CONVT2) {
+            if (convT2s_layer_ok<PolBF16>(ly.cin_p, ly.cout_p, false)) {
+                sb[ly.pk_off + convT2s_index<bf16_t>(tap, cis, co, ly.cin_p, ly.cout_p, false)] = f2bf(v);
+                sf[ly.pk_off + convT2s_index<float>(tap, cis, co, ly.cin_p, ly.cout_p, false)] = v;
+            }
+            if (convT2s_layer_ok<PolBF16>(ly.cout_p, ly.cin_p, true)) {
+                stb[ly.pk_off + convT2s_index<bf16_t>(tap, cis, co, ly.cin_p, ly.cout_p, true)] = f2bf(v);
+                stf[ly.pk_off + convT2s_index<float>(tap, cis, co, ly.cin_p, ly.cout_p, true)] = v;
+            }
+        }
         if (ly.kind == L_CONV3) {
             const bool fwd = conv3s_layer_ok(ly.cat_cp ? ly.cat_cp : ly.cin_p, ly.cat_cp ? ly.cin_p - ly.cat_cp : 0, ly.cout_p);
             const bool bwd = conv3s_layer_ok(ly.cout_p, 0, ly.cin_p);
@@ -446,7 +456,7 @@ static int autotune_impl(const no_net* net, int Hp, int Wp, int batch, const Fwd
     auto time_convT2 = [&](const Layer& lu, const T* x, T* y, int H, int W, float* ms_out) -> int {
         auto run = [&]() {
             return launch_convT2<P>(x, lu.cin_p, packed_w<P>(net, lu), packed_b<P>(net, lu), y, lu.cout_p, H, W,
-                                    batch, nullptr, s);
+                                    batch, nullptr, s, streamed_w<P>(net, lu));
         };
         HZ_TRY(run());
         HZ_TRY(hold());
@@ -766,7 +776,7 @@ static int layer_impl(const no_net* net, int layer, int batch, int H, int W, con
                                (typename P::Acc*)ws, streamed_w<P>(net, ly));
     }
     return launch_convT2<P>((const T*)x0, ly.cin_p, packed_w<P>(net, ly), packed_b<P>(net, ly), (T*)y, ly.cout_p,
-                            H, W, batch, nullptr, s);
+                            H, W, batch, nullptr, s, streamed_w<P>(net, ly));
 }
 }  // namespace hz
 

@@ -1523,7 +1523,8 @@ int launch_conv3_up(const typename P::T* x0, int c0, UpIn up, int c1, const type
 
 template <class P>
 int launch_convT2(const typename P::T* x, int cin_p, const typename P::T* w, const typename P::Acc* bias,
-                  typename P::T* y, int cout_p, int H, int W, int batch, const int* skip, hipStream_t s) {
+                  typename P::T* y, int cout_p, int H, int W, int batch, const int* skip, hipStream_t s,
+                  const void* wf) {
     const int ck = convT2_stage<P>(cin_p);
     constexpr int VE = 16 / sizeof(typename P::T);
     if (cout_p % 16 || ck < VE || cin_p % ck || ck % VE) {
@@ -1532,8 +1533,10 @@ int launch_convT2(const typename P::T* x, int cin_p, const typename P::T* w, con
     }
     if constexpr (std::is_same<P, PolBF16>::value) {
         // the weight-stationary form (16-channel blocks, 4-32 row segments per block) where the input
-        // channels fit one stage and it gives at least 256 blocks (the same result bits)
-        if (convT2_ws_ok<P>(cin_p, cout_p, 16)) {
+        // channels fit one stage and it gives at least 256 blocks (the same result bits); with a
+        // streamed pack only for 64 input channels, whose blocks are too short for the streamed form
+        // (64 -> 32 channels at 544^2: 33 us against 38; 128 -> 64 at 272^2: 26 us both)
+        if (convT2_ws_ok<P>(cin_p, cout_p, 16) && (!wf || cin_p <= 64)) {
             const int nt = H * ((W + 63) / 64);
             const int64_t ncb = cout_p / 16;
             int tpb = 32;
@@ -1545,6 +1548,14 @@ int launch_convT2(const typename P::T* x, int cin_p, const typename P::T* w, con
                 HZ_LAUNCH_CHECK();
                 return HZ_OK;
             }
+        }
+    }
+    if constexpr (!std::is_same<P, PolF64>::value) {
+        const int64_t npix = (int64_t)batch * H * W;
+        const int form = wf ? convT2s_pick<P>(cin_p, cout_p, false, npix) : 0;
+        if (form) {
+            ConvT2sArgs<P> g{x, cin_p, wf, bias, y, cout_p, nullptr, H, W, npix, skip};
+            return launch_convT2s<P>(form, g, false, s);
         }
     }
     const int tn = cout_p % 32 == 0 ? 32 : 16;
@@ -1687,7 +1698,7 @@ int launch_convT2_jobs(const TileJob* jobs, int njobs, const LayerIO* io, const 
                                  P::T*, int, int, int, bool, const int*, hipStream_t, Conv3Out, ConvCfg,       \
                                  P::Acc*, const void*);                                                        \
     template int launch_convT2<P>(const P::T*, int, const P::T*, const P::Acc*, P::T*, int, int, int, int,       \
-                                  const int*, hipStream_t);                                                    \
+                                  const int*, hipStream_t, const void*);                                       \
     template int launch_conv3_jobs<P>(const TileJob*, int, const LayerIO*, const P::T*, const P::Acc*, int, int, \
                                       int, int, int, bool, hipStream_t);                                       \
     template int launch_conv3_jobs_head<P>(const TileJob*, int, const LayerIO*, const P::T*, const P::Acc*, int,   \

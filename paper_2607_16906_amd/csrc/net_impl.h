@@ -191,18 +191,24 @@ inline const typename P::T* packed_wt(const no_net* net, const Layer& ly) {
     else if constexpr (sizeof(typename P::T) == 4) return net->wt_f32 + ly.pk_off;
     else return net->wt_f64 + ly.pk_off;
 }
-// streamed packs of a 3x3 layer (NULL where it has none): forward, data gradient
+// streamed packs of a 3x3 or transposed layer (NULL where it has none): forward, data gradient
 template <class P>
 inline const void* streamed_w(const no_net* net, const Layer& ly) {
     const int c0 = ly.cat_cp ? ly.cat_cp : ly.cin_p;
-    if (ly.kind != L_CONV3 || !conv3s_layer_ok(c0, ly.cin_p - c0, ly.cout_p)) return nullptr;
+    const bool has = ly.kind == L_CONV3    ? conv3s_layer_ok(c0, ly.cin_p - c0, ly.cout_p)
+                     : ly.kind == L_CONVT2 ? convT2s_layer_ok<P>(ly.cin_p, ly.cout_p, false)
+                                           : false;
+    if (!has) return nullptr;
     if constexpr (sizeof(typename P::T) == 2) return net->fs_bf + ly.pk_off;
     else if constexpr (sizeof(typename P::T) == 4) return net->fs_f32 + ly.pk_off;
     else return nullptr;
 }
 template <class P>
 inline const void* streamed_wt(const no_net* net, const Layer& ly) {
-    if (ly.kind != L_CONV3 || !conv3s_layer_ok(ly.cout_p, 0, ly.cin_p)) return nullptr;
+    const bool has = ly.kind == L_CONV3    ? conv3s_layer_ok(ly.cout_p, 0, ly.cin_p)
+                     : ly.kind == L_CONVT2 ? convT2s_layer_ok<P>(ly.cout_p, ly.cin_p, true)
+                                           : false;
+    if (!has) return nullptr;
     if constexpr (sizeof(typename P::T) == 2) return net->fst_bf + ly.pk_off;
     else if constexpr (sizeof(typename P::T) == 4) return net->fst_f32 + ly.pk_off;
     else return nullptr;
@@ -290,7 +296,7 @@ inline int unet_body(const no_net* net, const FwdBufs& b, int Hp, int Wp, int ba
                                       (T*)b.T1d[l], la.cout_p, H, W, batch, skip, s, ucfg));
         } else {
             HZ_TRY(launch_convT2<P>(Dn, lu.cin_p, packed_w<P>(net, lu), packed_b<P>(net, lu), (T*)b.U[l],
-                                    lu.cout_p, H / 2, W / 2, batch, skip, s));
+                                    lu.cout_p, H / 2, W / 2, batch, skip, s, streamed_w<P>(net, lu)));
             HZ_TRY(launch_conv3<P>((const T*)b.E[l], ce, (const T*)b.U[l], ce, packed_w<P>(net, la),
                                    packed_b<P>(net, la), (T*)b.T1d[l], la.cout_p, nullptr, H, W, batch, true, skip,
                                    s, Conv3Out(), net_cfg(net, li - 2, H, W, batch, prec_of<P>()), sb,

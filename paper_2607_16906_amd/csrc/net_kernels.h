@@ -302,6 +302,74 @@ __device__ __forceinline__ int xcd_linear(int p, int n) {
     return k * q + (k < r ? k : r) + i;
 }
 
+// Streamed-weights transposed convolution (net_convt.hip). Forms (id, 16-pixel blocks per wavefront,
+// 16-row blocks of M per wavefront, wavefronts along M, wavefronts along pixels).
+#define HZ_CONVT2S_FORMS(F) F(1, 4, 2, 4, 1) F(2, 2, 2, 4, 1) F(3, 4, 1, 4, 1) F(4, 2, 1, 4, 1)
+struct ConvT2sForm {
+    int px, mblk;   // pixels and 16-row blocks of M per block of threads
+};
+constexpr ConvT2sForm convT2s_form(int id) {
+#define HZ_CT(ID, PB, MB, WM, WP) \
+    if (id == ID) return ConvT2sForm{16 * PB * WP, MB * WM};
+    HZ_CONVT2S_FORMS(HZ_CT)
+#undef HZ_CT
+    return ConvT2sForm{0, 0};
+}
+// Layers (forward: K = KC input channels, M = 4 MC; data gradient: K = 4 KC output channels, M = MC) that
+// have a streamed pack: an even number of K operands and whole groups of 4 row blocks of M.
+template <class P>
+constexpr bool convT2s_layer_ok(int KC, int MC, bool dgrad) {
+    if (std::is_same<P, PolF64>::value) return false;
+    return dgrad ? KC > 0 && KC % 32 == 0 && MC % 64 == 0 : KC > 0 && KC % 64 == 0 && MC % 16 == 0;
+}
+// Form of a launch over npix pixels: the largest tile with at least 512 blocks (two per CU), else the
+// form with the most blocks (256 -> 128 channels at 37^2: form 1, 176 blocks, 6.6 us, form 4, 704 blocks,
+// 5.2 us; at 136^2: form 1, 1160 blocks, 17 us, form 4 35 us). Tiles of 256 rows of M or of 128 pixels
+// were never faster.
+template <class P>
+int convT2s_pick(int KC, int MC, bool dgrad, int64_t npix) {
+    if (!convT2s_layer_ok<P>(KC, MC, dgrad) || npix > INT32_MAX) return 0;
+    const int mblk = dgrad ? MC / 16 : MC / 4;
+    int best = 0;
+    for (int id : {1, 2, 3, 4}) {
+        const ConvT2sForm f = convT2s_form(id);
+        if (mblk % f.mblk || (id == 3 && mblk % 8 == 0)) continue;
+        best = id;
+        if ((npix + f.px - 1) / f.px * (mblk / f.mblk) >= 512) break;
+    }
+    return best;
+}
+// Position of weight (parity ab, input channel ci, output channel co) in the streamed packs of T.
+template <typename T>
+__host__ __device__ constexpr int64_t convT2s_index(int ab, int ci, int co, int cin_p, int cout_p, bool dgrad) {
+    constexpr int CK = 64 / (int)sizeof(T), VE = 16 / (int)sizeof(T);
+    const int kc = dgrad ? co : ci, row = dgrad ? ci : co;
+    const int c = kc % CK;
+    const int lg = sizeof(T) == 2 ? c / VE : c % 4, e = sizeof(T) == 2 ? c % VE : c / 4;
+    const int nk = dgrad ? 4 * cout_p / CK : cin_p / CK;
+    const int ks = dgrad ? kc / CK * 4 + ab : kc / CK;
+    const int mb = dgrad ? row / 16 : ((ab >> 1) * (cout_p / 16) + row / 16) * 2 + (ab & 1);
+    return ((int64_t)mb * nk + ks) * (1024 / (int)sizeof(T)) + (lg * 16 + row % 16) * VE + e;
+}
+template <class P>
+struct ConvT2sArgs {
+    const typename P::T* x;   // forward: input pixels; data gradient: G on the fine grid
+    int KC;                   // channels of x
+    const void* wf;           // streamed pack
+    const float* bias;        // forward
+    typename P::T* y;
+    int MC;                   // channels of y
+    const typename P::T* mask;   // data gradient: y is zero where its entry is <= 0
+    int H, W;                 // coarse grid
+    int64_t npix;             // coarse pixels of the batch
+    const int* skip;
+    const TileJob* jobs = nullptr;   // ragged batch (forward): job = (sys, M group, pixel tile)
+    int njobs = 0;
+    const LayerIO* io = nullptr;
+};
+template <class P>
+int launch_convT2s(int form, const ConvT2sArgs<P>& g, bool dgrad, hipStream_t s);
+
 // Host-side launch helpers (defined in net_fwd.hip), one per precision.
 // conv3: y = act(conv3x3(concat[x0, x1]) + b) (+ pooled copy); batch samples along grid z. wf: the
 // layer's streamed pack, if it has one.
@@ -361,9 +429,11 @@ template <class P>
 int launch_conv3_up(const typename P::T* x0, int c0, UpIn up, int c1, const typename P::T* w,
                     const typename P::Acc* bias, typename P::T* y, int cout_p, int H, int W, int batch,
                     const int* skip, hipStream_t s, ConvCfg cfg);
-// convT2: y[2i+a][2j+b] = sum_c x[i][j][c] w[a][b][.][c] + b
+// convT2: y[2i+a][2j+b] = sum_c x[i][j][c] w[a][b][.][c] + b; wf: the layer's streamed pack, if it has one
+// (the same result bits)
 template <class P>
 int launch_convT2(const typename P::T* x, int cin_p, const typename P::T* w, const typename P::Acc* bias,
-                  typename P::T* y, int cout_p, int H, int W, int batch, const int* skip, hipStream_t s);
+                  typename P::T* y, int cout_p, int H, int W, int batch, const int* skip, hipStream_t s,
+                  const void* wf = nullptr);
 
 }  // namespace hz

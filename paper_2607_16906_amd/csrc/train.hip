@@ -1114,6 +1114,15 @@ static int dgrad_conv3(const no_net* net, const Layer& ly, const typename P::T* 
 template <class P>
 static int dgrad_convT(const no_net* net, const Layer& ly, const typename P::T* G, const typename P::T* xmask,
                        typename P::T* gx, int H, int W, int B, hipStream_t s) {
+    if constexpr (!std::is_same<P, PolF64>::value) {
+        const void* wf = streamed_wt<P>(net, ly);
+        const int64_t npix = (int64_t)B * H * W;
+        const int form = wf ? convT2s_pick<P>(ly.cout_p, ly.cin_p, true, npix) : 0;
+        if (form) {
+            ConvT2sArgs<P> g{G, ly.cout_p, wf, nullptr, gx, ly.cin_p, xmask, H, W, npix, nullptr};
+            return launch_convT2s<P>(form, g, true, s);
+        }
+    }
     const int ck = std::min(P::CK, ly.cout_p);
     const int tn = ly.cin_p % 32 == 0 ? 32 : 16;
     dim3 grid((W + 63) / 64, H, (ly.cin_p / tn) * B);
@@ -1301,7 +1310,7 @@ static int loss_backward_impl(const no_net* net, int B, const hz_problem* const*
             // the level's upsampled tensor and first-convolution output, as the forward pass made them
             const T* Dn0 = l + 1 == lv - 1 ? (const T*)t.f.E[l + 1] : (const T*)t.f.D[l + 1];
             HZ_TRY(launch_convT2<P>(Dn0, lu.cin_p, packed_w<P>(net, lu), packed_b<P>(net, lu), (T*)t.f.U[l],
-                                    lu.cout_p, H / 2, W / 2, B, nullptr, s));
+                                    lu.cout_p, H / 2, W / 2, B, nullptr, s, streamed_w<P>(net, lu)));
             HZ_TRY(launch_conv3<P>((const T*)t.f.E[l], lu.cout_p, (const T*)t.f.U[l], lu.cout_p, packed_w<P>(net, la),
                                    packed_b<P>(net, la), (T*)t.f.T1d[l], la.cout_p, nullptr, H, W, B, true, nullptr,
                                    s, Conv3Out(), net_cfg(net, dec_a[l], H, W, B, prec_of<P>()),
