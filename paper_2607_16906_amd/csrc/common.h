@@ -100,13 +100,27 @@ template <> __host__ __device__ inline double2 from_d2<double2>(double2 a) { ret
 
 typedef uint16_t bf16_t;
 
-// Round-to-nearest-even FP32 -> BF16, NaN preserving (quiet bit set).
+// Round-to-nearest-even FP32 -> BF16, NaN preserving (quiet bit set). The device takes the conversion
+// instruction, one for a pair of values where the bit arithmetic takes some eight per value; it gives
+// the same bits for every one of the 2^32 inputs.
+#if defined(__HIP_DEVICE_COMPILE__)
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
+typedef __attribute__((ext_vector_type(2))) float f32x2_t;
+__device__ inline uint32_t f2bf_pair(float lo, float hi) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{lo, hi}, bf16x2_t));
+}
+__device__ inline bf16_t f2bf(float f) { return (bf16_t)(f2bf_pair(f, f) & 0xffffu); }
+#else
 __host__ __device__ inline bf16_t f2bf(float f) {
     uint32_t u = __builtin_bit_cast(uint32_t, f);
     if ((u & 0x7f800000u) == 0x7f800000u && (u & 0x7fffffu)) return (bf16_t)((u >> 16) | 0x40);
     u += 0x7fffu + ((u >> 16) & 1u);
     return (bf16_t)(u >> 16);
 }
+__host__ __device__ inline uint32_t f2bf_pair(float lo, float hi) {
+    return (uint32_t)f2bf(lo) | ((uint32_t)f2bf(hi) << 16);
+}
+#endif
 __host__ __device__ inline float bf2f(bf16_t b) { return __builtin_bit_cast(float, ((uint32_t)b) << 16); }
 
 // ----------------------------------------------------------------- reductions

@@ -141,7 +141,10 @@ __global__ void k_head_dgrad(const float2* __restrict__ gz, const float* __restr
     __attribute__((aligned(16))) T out[VE];
 #pragma unroll
     for (int k = 0; k < VE; ++k) {
-        Acc v = (Acc)g.x * P::val(wh[c0 + k]) + (Acc)g.y * P::val(wh[cin_p + c0 + k]);
+        // (BF16: the contraction spelled out, the same one for every entry)
+        Acc v;
+        if constexpr (sizeof(T) == 2) v = fmaf(g.x, P::val(wh[c0 + k]), g.y * P::val(wh[cin_p + c0 + k]));
+        else v = (Acc)g.x * P::val(wh[c0 + k]) + (Acc)g.y * P::val(wh[cin_p + c0 + k]);
         if (!(P::val(d[k]) > Acc(0))) v = Acc(0);
         out[k] = P::cvt(v);
     }
