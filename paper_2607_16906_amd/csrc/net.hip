@@ -196,19 +196,6 @@ void net_padded_dims(const no_net* net, const hz_problem* p, int* Hp, int* Wp) {
 
 // ------------------------------------------------------------------ pack / head
 
-// s = ||v|| / sqrt(n) from norm partials; sc[0] = s, sc[1] = 1 / s (0 when s = 0).
-__global__ void k_scale_factor(const double2* part, int nblk, int64_t n, double* sc, const int* skip) {
-    if (skip && *skip) return;
-    double a = 0;
-    for (int q = threadIdx.x; q < nblk; q += 64) a += part[q].x;
-    a = wave_sum(a);
-    if (threadIdx.x == 0) {
-        const double s = sqrt(a / (double)n);
-        sc[0] = s;
-        sc[1] = s > 0 ? 1.0 / s : 0.0;
-    }
-}
-
 // z = s (out_0 + i out_1), out_k = sum_c D0[c] Wh[k][c] + bh[k], on the grid only.
 template <class P, typename C>
 __global__ void k_head(const typename P::T* __restrict__ D, int cin_p, const typename P::T* __restrict__ wh,
@@ -259,12 +246,14 @@ static int precond_impl(const no_net* net, const hz_problem* p, bool c128, const
     Split sp = krylov_split(n);
     // s = ||v|| / sqrt(n); a unit-norm Krylov vector has s = 1 / sqrt(n) without a reduction
     const double fixed_s = unit_norm ? 1.0 / sqrt((double)n) : 0.0;
-    double* scp = nparts ? nparts->sc : b.sc;   // [s, 1/s]
+    // otherwise the packing launch adds the norm's partial sums itself (every block the same few
+    // hundred values, in the same order: no launch for one block to do it)
+    NormParts own{b.part, sp.nblk, 1, b.sc};
     if (!unit_norm && !nparts) {
         HZ_TRY(launch_norm_partials(c128, v, n, sp, b.part, 1, 0, skip, s));
-        hipLaunchKernelGGL(k_scale_factor, dim3(1), dim3(64), 0, s, b.part, sp.nblk, n, b.sc, skip);
-        HZ_LAUNCH_CHECK();
+        nparts = &own;
     }
+    double* scp = nparts ? nparts->sc : b.sc;   // [s, 1/s]
     const unsigned gp = (unsigned)(((int64_t)Hp * Wp + 255) / 256);
     if (c128)
         hipLaunchKernelGGL((k_pack<P, double2>), dim3(gp), dim3(256), 0, s, (const double2*)v, scp, p->cnd, p->sigx,
