@@ -212,7 +212,9 @@ int no_set_layer_variant(const no_net* net, int layer, no_prec prec, int batch, 
  * transposed convolution (the decoder's upsampling, Section 3.1) inside the blocks of the
  * level's first 3x3 convolution instead of storing it. mode 0: never; 1: always where it
  * applies; 2 (the default): where no_autotune measured it faster than the two separate layers
- * (untuned sizes run them separately). Every choice gives the same result bits. Not
+ * (untuned sizes run them separately). Modes 1 and 2 also run level 0 of a network with 32
+ * base channels (BF16) as two launches, its encoder pair and its decoder with the output layer;
+ * mode 0 runs every layer as its own launch. Every choice gives the same result bits. Not
  * thread-safe against concurrent solves on the handle. Errors: NULL network, mode not 0-2. */
 int no_set_fused_upsampling(no_net* net, int mode);
 

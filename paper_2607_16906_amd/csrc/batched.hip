@@ -430,7 +430,8 @@ struct HostTables {
     std::vector<std::vector<TileJob>> cjobs;
     std::vector<int> tn, rpw;
     std::vector<char> ws;   // layer in the weight-stationary form
-    std::vector<int> st;    // streamed-weights form of a 3x3 layer (0: none)
+    std::vector<int> st;    // streamed-weights form of a 3x3 or transposed layer (0: none)
+    bool fuse0 = false;     // level 0 as its fused encoder (jobs of layer 1) and decoder (of the last 3x3 layer)
 };
 
 // Launch form of a 3x3 layer over a ragged batch with `tiles16` 16 x 16 and `tiles8` 8 x 16 pixel tiles.
@@ -499,10 +500,12 @@ static void build_tables(const BatchPlan<P>& B, const no_net* net, const std::ve
     h.rpw.assign(nl, 2);
     h.ws.assign(nl, 0);
     h.st.assign(nl, 0);
+    h.fuse0 = net->fuse_up != 0 && head_fused(net) && level0_fusable<P>(net);
     for (int li = 0; li < nl - 1; ++li) {
         const Layer& ly = net->layers[li];
         const int l = lvl[li];
         const bool convT = role[li] == 2;
+        const bool lev0 = h.fuse0 && (li < 2 || li >= nl - 4);
         int64_t tiles = 0, tiles16 = 0;
         for (int s : active) {
             const int H = B.S[s].Hp >> l, W = B.S[s].Wp >> l;
@@ -558,6 +561,11 @@ static void build_tables(const BatchPlan<P>& B, const no_net* net, const std::ve
                 case 3: io.x0 = fb.E[l]; io.x1 = fb.U[l]; io.y = fb.T1d[l]; break;
                 case 4: io.x0 = fb.T1d[l]; io.y = fb.D[l]; break;
             }
+            if (lev0 && li == 1) io.x0 = fb.X;
+            if (lev0 && li == nl - 2) {
+                io.x0 = fb.E[0];
+                io.x1 = lv > 2 ? fb.D[1] : fb.E[1];
+            }
             if (fhead) {
                 const KDesc& d = B.S[s].d;
                 io.y = nullptr;
@@ -572,7 +580,11 @@ static void build_tables(const BatchPlan<P>& B, const no_net* net, const std::ve
         // to a contiguous range of jobs, so they share the tile's input in one L2)
         for (int s : active) {
             const int H = B.S[s].Hp >> l, W = B.S[s].Wp >> l;
-            if (convT && st) {   // (sys, M group, pixel tile)
+            if (lev0) {   // one launch each for the encoder and the decoder, tiles of LEVEL0_TILE
+                if (li == 1 || li == nl - 2)
+                    for (int ty = 0; ty < H; ty += LEVEL0_TILE)
+                        for (int tx = 0; tx < W; tx += LEVEL0_TILE) h.cjobs[li].push_back(TileJob{s, 0, ty, tx});
+            } else if (convT && st) {   // (sys, M group, pixel tile)
                 const ConvT2sForm f = convT2s_form(st);
                 for (int t = 0; t < (H * W + f.px - 1) / f.px; ++t)
                     for (int gm = 0; gm < ly.cout_p / 4 / f.mblk; ++gm) h.cjobs[li].push_back(TileJob{s, gm, t, 0});
@@ -637,7 +649,14 @@ static int net_step(const BatchPlan<P>& B, const HostTables<P>& h, const no_net*
         const Layer& ly = net->layers[li];
         const int nj = (int)h.cjobs[li].size();
         const bool hd = fhead && li == nl - 2;
-        if (role[li] == 2 && h.st[li]) {
+        if (h.fuse0 && (li < 2 || li >= nl - 4)) {
+            if constexpr (std::is_same<P, PolBF16>::value) {
+                if (li == 1) HZ_TRY(launch_level0_enc_jobs(t.cjobs[li], nj, t.io[li], level0_enc(net), s));
+                if (hd)
+                    HZ_TRY(launch_level0_dec_jobs(t.cjobs[li], nj, t.io[li], level0_dec(net), col,
+                                                  std::is_same<C, double2>::value, s));
+            }
+        } else if (role[li] == 2 && h.st[li]) {
             if constexpr (!std::is_same<P, PolF64>::value) {
                 ConvT2sArgs<P> g{};
                 g.KC = ly.cin_p;

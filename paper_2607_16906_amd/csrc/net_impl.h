@@ -255,6 +255,25 @@ inline int paper8_body(const no_net* net, const FwdBufs& b, int Hp, int Wp, int 
     return HZ_OK;
 }
 
+// Whether level 0 runs as the fused encoder and decoder launches (net_level0.hip).
+template <class P>
+inline bool level0_fusable(const no_net* net) {
+    const std::vector<Layer>& L = net->layers;
+    const size_t n = L.size();
+    return std::is_same<P, PolBF16>::value && net->a.kind == NO_ARCH_UNET3 && net->a.levels >= 2 && L[0].cin_p == 8 &&
+           L[0].cout_p == 32 && L[n - 4].cin_p == 64 && L[n - 1].cin_p == 32;
+}
+inline Level0Enc level0_enc(const no_net* net) {
+    const Layer &a = net->layers[0], &b = net->layers[1];
+    return Level0Enc{net->w_bf + a.pk_off, net->b_f32 + a.bias_off, net->fs_bf + b.pk_off, net->b_f32 + b.bias_off};
+}
+inline Level0Dec level0_dec(const no_net* net) {
+    const size_t n = net->layers.size();
+    const Layer &u = net->layers[n - 4], &a = net->layers[n - 3], &b = net->layers[n - 2], &h = net->layers[n - 1];
+    return Level0Dec{net->fs_bf + u.pk_off, net->b_f32 + u.bias_off, net->fs_bf + a.pk_off, net->b_f32 + a.bias_off,
+                     net->fs_bf + b.pk_off, net->b_f32 + b.bias_off, net->w_bf + h.pk_off,  net->b_f32 + h.bias_off};
+}
+
 template <class P>
 inline int unet_body(const no_net* net, const FwdBufs& b, int Hp, int Wp, int batch, const int* skip, hipStream_t s,
                      const Conv3Out* head = nullptr) {
@@ -264,11 +283,18 @@ inline int unet_body(const no_net* net, const FwdBufs& b, int Hp, int Wp, int ba
     const int lv = net->a.levels;
     const std::vector<Layer>& Ls = net->layers;
     int li = 0;
+    // (the fused-decoder choice covers this too: with 0 every layer is its own launch)
+    const bool fuse0 = head && batch == 1 && b.fuse_up != 0 && level0_fusable<P>(net);
     for (int l = 0; l < lv; ++l) {
         const int H = Hp >> l, W = Wp >> l;
         const Layer& la = Ls[li++];
         const Layer& lb = Ls[li++];
         const T* in = l == 0 ? (const T*)b.X : (const T*)b.P[l];
+        if (l == 0 && fuse0) {
+            if constexpr (std::is_same<P, PolBF16>::value)
+                HZ_TRY(launch_level0_enc(in, level0_enc(net), (T*)b.E[0], (T*)b.P[1], H, W, skip, s));
+            continue;
+        }
         HZ_TRY(launch_conv3<P>(in, la.cin_p, nullptr, 0, packed_w<P>(net, la), packed_b<P>(net, la), (T*)b.T1[l],
                                la.cout_p, nullptr, H, W, batch, true, skip, s, Conv3Out(),
                                net_cfg(net, li - 2, H, W, batch, prec_of<P>()), sb, streamed_w<P>(net, la)));
@@ -281,6 +307,11 @@ inline int unet_body(const no_net* net, const FwdBufs& b, int Hp, int Wp, int ba
     const T* Dn = (const T*)b.E[lv - 1];
     for (int l = lv - 2; l >= 0; --l) {
         const int H = Hp >> l, W = Wp >> l;
+        if (l == 0 && fuse0) {
+            if constexpr (std::is_same<P, PolBF16>::value)
+                HZ_TRY(launch_level0_dec((const T*)b.E[0], Dn, level0_dec(net), H, W, *head, skip, s));
+            break;
+        }
         const Layer& lu = Ls[li++];
         const Layer& la = Ls[li++];
         const Layer& lb = Ls[li++];

@@ -44,10 +44,7 @@ struct PolBF16 {
     // the 4 registers of a lane are 4 consecutive channels: one 8-byte store at p = &row_of(lg, 0)
     static constexpr bool CONTIG = true;
     __device__ static void store4(T* p, const Acc (&v)[4]) {
-        uint2 u;
-        u.x = (uint32_t)f2bf(v[0]) | ((uint32_t)f2bf(v[1]) << 16);
-        u.y = (uint32_t)f2bf(v[2]) | ((uint32_t)f2bf(v[3]) << 16);
-        *(uint2*)p = u;
+        *(uint2*)p = uint2{f2bf_pair(v[0], v[1]), f2bf_pair(v[2], v[3])};
     }
 };
 
@@ -369,6 +366,35 @@ struct ConvT2sArgs {
 };
 template <class P>
 int launch_convT2s(int form, const ConvT2sArgs<P>& g, bool dgrad, hipStream_t s);
+
+// Level 0 of the network in two launches (net_level0.hip; BF16, 32 channels, inference): weights of its
+// encoder pair (first layer packed [tap][32][8], second one streamed) and of its decoder (transposed
+// layer 64 -> 32, the two 3x3 layers streamed, output head).
+constexpr int LEVEL0_TILE = 14;   // output pixels per block, each way
+struct Level0Enc {
+    const bf16_t* wa;
+    const float* ba;
+    const void* wfb;
+    const float* bb;
+};
+struct Level0Dec {
+    const void* wfu;
+    const float* bu;
+    const void* wfa;
+    const float* ba;
+    const void* wfb;
+    const float* bb;
+    const bf16_t* head_w;   // [2][32]
+    const float* head_b;
+};
+int launch_level0_enc(const bf16_t* x, const Level0Enc& w, bf16_t* y, bf16_t* ypool, int H, int W, const int* skip,
+                      hipStream_t s);
+int launch_level0_dec(const bf16_t* e, const bf16_t* d, const Level0Dec& w, int H, int W, const Conv3Out& head,
+                      const int* skip, hipStream_t s);
+// Over a job table: job = (sys, -, tile row, tile column); encoder x0, y, ypool; decoder x0 = E, x1 = D, z.
+int launch_level0_enc_jobs(const TileJob* jobs, int njobs, const LayerIO* io, const Level0Enc& w, hipStream_t s);
+int launch_level0_dec_jobs(const TileJob* jobs, int njobs, const LayerIO* io, const Level0Dec& w, int col, bool c128,
+                           hipStream_t s);
 
 // Host-side launch helpers (defined in net_fwd.hip), one per precision.
 // conv3: y = act(conv3x3(concat[x0, x1]) + b) (+ pooled copy); batch samples along grid z. wf: the
