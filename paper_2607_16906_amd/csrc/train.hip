@@ -25,6 +25,7 @@
 #include "net_impl.h"
 #include "problem.h"
 #include "stencil_impl.h"
+#include "train_wgrad.h"
 
 namespace hz {
 
@@ -232,231 +233,9 @@ __global__ void k_head_reduce(const float* __restrict__ part, int nchunk, int ci
 
 // ------------------------------------------------------------------ weight gradients
 
-// 3x3: block (ci tile of 16, co tile of 16, chunk z) accumulates, over its 8 x 16 pixel tiles,
-// dW[co][ci][tap] into part[z][co][ci][tap] and (ci tile 0) db[co] into partb[z][co].
-template <class P>
-__global__ __launch_bounds__(TT) void k_wgrad3(const typename P::T* __restrict__ G, int cout_p,
-                                               const typename P::T* __restrict__ x0, int c0,
-                                               const typename P::T* __restrict__ x1, int c1, int H, int W,
-                                               int ntiles, int tpc, float* __restrict__ part,
-                                               float* __restrict__ partb) {
-    __shared__ float gs[128][17];
-    __shared__ float xs[180][17];
-    const int cin_p = c0 + c1;
-    const int ci0 = blockIdx.x * 16, co0 = blockIdx.y * 16;
-    const int z = blockIdx.z;
-    const int tco = threadIdx.x >> 4, tci = threadIdx.x & 15;
-    const int tx_n = (W + 15) / 16, ty_n = (H + 7) / 8;
-    const int per_img = tx_n * ty_n;
-    float acc[9], accb = 0;
-#pragma unroll
-    for (int t = 0; t < 9; ++t) acc[t] = 0;
-    const int64_t plane = (int64_t)H * W;
-    const int t_end = min(ntiles, (z + 1) * tpc);
-    for (int tile = z * tpc; tile < t_end; ++tile) {
-        const int b = tile / per_img, r = tile - b * per_img;
-        const int ty0 = (r / tx_n) * 8, tx0 = (r % tx_n) * 16;
-        __syncthreads();
-        for (int v = threadIdx.x; v < 128 * 16; v += TT) {
-            const int px = v >> 4, c = v & 15;
-            const int gy = ty0 + (px >> 4), gx = tx0 + (px & 15);
-            float val = 0.f;
-            if (gy < H && gx < W) val = (float)P::val(G[((int64_t)b * plane + (int64_t)gy * W + gx) * cout_p + co0 + c]);
-            gs[px][c] = val;
-        }
-        for (int v = threadIdx.x; v < 180 * 16; v += TT) {
-            const int px = v >> 4, c = v & 15;
-            const int gy = ty0 + px / 18 - 1, gx = tx0 + px % 18 - 1;
-            const int ci = ci0 + c;
-            float val = 0.f;
-            if (gy >= 0 && gy < H && gx >= 0 && gx < W && ci < cin_p) {
-                const int64_t pix = (int64_t)b * plane + (int64_t)gy * W + gx;
-                val = (float)P::val(ci < c0 ? x0[pix * c0 + ci] : x1[pix * c1 + ci - c0]);
-            }
-            xs[px][c] = val;
-        }
-        __syncthreads();
-        for (int px = 0; px < 128; ++px) {
-            const float g = gs[px][tco];
-            const int py = px >> 4, pxx = px & 15;
-#pragma unroll
-            for (int t = 0; t < 9; ++t) acc[t] += g * xs[(py + t / 3) * 18 + pxx + t % 3][tci];
-            accb += g;
-        }
-    }
-    const int co = co0 + tco, ci = ci0 + tci;
-    if (ci < cin_p) {
-        float* dst = part + (((int64_t)z * cout_p + co) * cin_p + ci) * 9;
-#pragma unroll
-        for (int t = 0; t < 9; ++t) dst[t] = acc[t];
-    }
-    if (blockIdx.x == 0 && tci == 0) partb[(int64_t)z * cout_p + co] = accb;
-}
-
-// 8 x 8 transpose of 16-bit elements: r[p] holds elements 0..7 of row p; o[k] receives element k
-// of rows 0..7 (row p in its element p)
-__device__ __forceinline__ void wg_transpose8(const uint4 (&r)[8], uint4 (&o)[8]) {
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        uint32_t wv[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const uint32_t a = (&r[2 * j].x)[k >> 1], c = (&r[2 * j + 1].x)[k >> 1];
-            wv[j] = (k & 1) ? ((a >> 16) | (c & 0xffff0000u)) : ((a & 0xffffu) | (c << 16));
-        }
-        o[k] = uint4{wv[0], wv[1], wv[2], wv[3]};
-    }
-}
-
-// 3x3 on the matrix cores (BF16 operands, FP32 accumulation): for every tap (dy, dx),
-// dW[co][ci][tap] = sum_p G[p][co] X[p + (dy - 1, dx - 1)][ci] is a product with the pixels as
-// the reduction index. Block: 32 output x 32 input channels over its chunk of 8 x 16 pixel
-// tiles. Each tile is staged in LDS transposed (pixels contiguous per channel) so that a lane's
-// 8 consecutive reduction elements are one 16-byte read; the input patch is stored three times,
-// shifted by dx, to keep those reads aligned. Wavefront w owns the 16 x 16 channel pair
-// (w / 2, w % 2) for all 9 taps. Partials and bias sums as in k_wgrad3.
 constexpr int WG_CO = 32, WG_CI = 32;
-constexpr int WG_GS = 128 + 8;              // LDS row of Gt: 128 pixels (+16 B)
-constexpr int WG_XS = 10 * 16 + 8;          // LDS plane of one channel of Xt: 10 rows x 16 (+16 B)
 
-__global__ __launch_bounds__(TT) void k_wgrad3_mfma(const bf16_t* __restrict__ G, int cout_p,
-                                                    const bf16_t* __restrict__ x0, int c0,
-                                                    const bf16_t* __restrict__ x1, int c1, int H, int W,
-                                                    int ntiles, int tpc, float* __restrict__ part,
-                                                    float* __restrict__ partb) {
-    __shared__ __attribute__((aligned(16))) bf16_t gt[WG_CO * WG_GS];
-    __shared__ __attribute__((aligned(16))) bf16_t xt[3 * WG_CI * WG_XS];
-    const int cin_p = c0 + c1;
-    const int ci0 = blockIdx.x * WG_CI, co0 = blockIdx.y * WG_CO;
-    const int z = blockIdx.z;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int lr = lane & 15, kg = lane >> 4;
-    const int cob = wv >> 1, cib = wv & 1;
-    const int tx_n = (W + 15) / 16, ty_n = (H + 7) / 8;
-    const int per_img = tx_n * ty_n;
-    const int64_t plane = (int64_t)H * W;
-    f32x4_t acc[9];
-#pragma unroll
-    for (int t = 0; t < 9; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[t][r] = 0.f;
-    float accb = 0.f;                            // bias: thread sums 16 pixels of channel threadIdx.x / 8
-    const int t_beg = z * tpc, t_end = min(ntiles, (z + 1) * tpc);
-    // G tile (128 pixels x 32 channels) and the three shifted copies of the input patch, staged
-    // transposed: a thread loads its unit's pixel vectors into registers (the next tile's while the
-    // matrix cores work on this one), transposes 8 pixels x 8 channels at a time (wg_transpose8)
-    // and writes 8 channel rows of 8 pixels as 16-byte stores (the same LDS contents as
-    // element-wise transposing stores). Units [0, 64): G, 8 pixels; [64, 144): 10 pixels of one
-    // patch row (columns 8 h .. 8 h + 9), from which the three copies take their 8-pixel windows.
-    constexpr int NU = 16 * 4 + 10 * 2 * 4;
-    static_assert(NU <= TT, "one unit per thread");
-    uint4 rg[10];
-    auto gload = [&](int tile) {
-        const int b = tile / per_img, r = tile - b * per_img;
-        const int ty0 = (r / tx_n) * 8, tx0 = (r % tx_n) * 16;
-        const int u = threadIdx.x;
-        if (u >= NU) return;
-        const int part8 = u & 3;
-        if (u < 16 * 4) {   // G: pixels 8 pg .. 8 pg + 7 of the tile (row pg / 2, columns 8 (pg % 2) ..)
-            const int pg = u >> 2;
-            const int gy = ty0 + (pg >> 1), gx0 = tx0 + 8 * (pg & 1);
-            const int co = co0 + part8 * 8;
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                rg[k] = uint4{0, 0, 0, 0};
-                if (gy < H && gx0 + k < W && co < cout_p)
-                    rg[k] = *(const uint4*)(G + ((int64_t)b * plane + (int64_t)gy * W + gx0 + k) * cout_p + co);
-            }
-        } else {            // X: patch row py, patch columns 8 h .. 8 h + 9
-            const int q = u - 16 * 4;
-            const int h = (q >> 2) & 1, py = q >> 3;
-            const int gy = ty0 + py - 1, gx0 = tx0 + 8 * h - 1;
-            const int ci = ci0 + part8 * 8;
-#pragma unroll
-            for (int k = 0; k < 10; ++k) {
-                const int gx = gx0 + k;
-                rg[k] = uint4{0, 0, 0, 0};
-                if (gy >= 0 && gy < H && gx >= 0 && gx < W && ci < cin_p) {
-                    const int64_t pix = (int64_t)b * plane + (int64_t)gy * W + gx;
-                    rg[k] = *(const uint4*)(ci < c0 ? x0 + pix * c0 + ci : x1 + pix * c1 + (ci - c0));
-                }
-            }
-        }
-    };
-    auto put = [&](bf16_t* dst, int stride, int off) {   // the 8 pixels rg[off ..] transposed to dst
-        uint4 w8[8], o[8];
-#pragma unroll
-        for (int k = 0; k < 8; ++k) w8[k] = rg[off + k];
-        wg_transpose8(w8, o);
-#pragma unroll
-        for (int k = 0; k < 8; ++k) *(uint4*)(dst + k * stride) = o[k];
-    };
-    auto lstore = [&]() {
-        const int u = threadIdx.x;
-        if (u >= NU) return;
-        const int part8 = u & 3;
-        if (u < 16 * 4) {
-            put(&gt[(part8 * 8) * WG_GS + 8 * (u >> 2)], WG_GS, 0);
-        } else {            // copy dx, columns 8 h .. 8 h + 7 hold patch columns 8 h + dx ..
-            const int q = u - 16 * 4;
-            const int h = (q >> 2) & 1, py = q >> 3;
-#pragma unroll
-            for (int dx = 0; dx < 3; ++dx)
-                put(&xt[(dx * WG_CI + part8 * 8) * WG_XS + py * 16 + 8 * h], WG_XS, dx);
-        }
-    };
-    if (t_beg < t_end) gload(t_beg);
-    for (int tile = t_beg; tile < t_end; ++tile) {
-        __syncthreads();   // the previous tile's reads of the LDS are done
-        lstore();
-        __syncthreads();
-        if (tile + 1 < t_end) gload(tile + 1);
-        if (blockIdx.x == 0) {
-            const int co = threadIdx.x >> 3, seg = threadIdx.x & 7;
-#pragma unroll
-            for (int k = 0; k < 16; ++k) accb += bf2f(gt[co * WG_GS + seg * 16 + k]);
-        }
-        // 4 reduction steps of 32 pixels (step s: tile rows 2s, 2s + 1), every tap's accumulator
-        // taking the steps in order. The input fragment of step s and row offset dy starts at patch
-        // row 2s + dy: per column offset dx, the 9 distinct fragments are read once for all steps.
-        bf16x8_t a[4];
-#pragma unroll
-        for (int s = 0; s < 4; ++s) a[s] = PolBF16::load(&gt[(cob * 16 + lr) * WG_GS + 32 * s + 8 * kg]);
-#pragma unroll
-        for (int dx = 0; dx < 3; ++dx) {
-            bf16x8_t bq[9];
-#pragma unroll
-            for (int q = 0; q < 9; ++q)
-                bq[q] = PolBF16::load(&xt[(dx * WG_CI + cib * 16 + lr) * WG_XS + (q + (kg >> 1)) * 16 + 8 * (kg & 1)]);
-#pragma unroll
-            for (int s = 0; s < 4; ++s)
-#pragma unroll
-                for (int dy = 0; dy < 3; ++dy) acc[dy * 3 + dx] = PolBF16::mma(a[s], bq[2 * s + dy], acc[dy * 3 + dx]);
-        }
-    }
-    // lane holds D[co = co0 + 16 cob + 4 kg + r][ci = ci0 + 16 cib + lr] of every tap
-    const int ci = ci0 + cib * 16 + lr;
-    if (ci < cin_p) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int co = co0 + cob * 16 + 4 * kg + r;
-            if (co < cout_p) {
-                float* dst = part + (((int64_t)z * cout_p + co) * cin_p + ci) * 9;
-#pragma unroll
-                for (int t = 0; t < 9; ++t) dst[t] = acc[t][r];
-            }
-        }
-    }
-    if (blockIdx.x == 0) {
-        accb += __shfl_xor(accb, 1, 64);
-        accb += __shfl_xor(accb, 2, 64);
-        accb += __shfl_xor(accb, 4, 64);
-        const int co = co0 + (threadIdx.x >> 3);
-        if ((threadIdx.x & 7) == 0 && co < cout_p) partb[(int64_t)z * cout_p + co] = accb;
-    }
-}
-
-// The same product in FP32 on the matrix cores (v_mfma_f32_16x16x4_f32: one reduction element
+// 3x3 weight gradient in FP32 on the matrix cores (v_mfma_f32_16x16x4_f32: one reduction element
 // per lane, 4 pixels per instruction). Block, tiles, partials and bias sums as in k_wgrad3_mfma;
 // the transposed LDS copies hold FP32 values, and a single copy of the 10 x 18 input patch serves
 // every dx since a lane reads one value. Row pitches of 130 and 194 floats (2 mod 32) make the 32
@@ -573,9 +352,8 @@ __global__ __launch_bounds__(TT) void k_wgrad3_mfma_f32(const float* __restrict_
         for (int r = 0; r < 4; ++r) {
             const int co = co0 + cob * 16 + 4 * kg + r;
             if (co < cout_p) {
-                float* dst = part + (((int64_t)z * cout_p + co) * cin_p + ci) * 9;
 #pragma unroll
-                for (int t = 0; t < 9; ++t) dst[t] = acc[t][r];
+                for (int t = 0; t < 9; ++t) part[(((int64_t)z * 9 + t) * cout_p + co) * cin_p + ci] = acc[t][r];
             }
         }
     }
@@ -635,139 +413,15 @@ __global__ __launch_bounds__(TT) void k_wgradT(const typename P::T* __restrict__
         }
     }
     const int co = co0 + tco, ci = ci0 + tci;
-    float* dst = part + (((int64_t)z * cout_p + co) * cin_p + ci) * 4;
 #pragma unroll
-    for (int ab = 0; ab < 4; ++ab) dst[ab] = acc[ab];
+    for (int ab = 0; ab < 4; ++ab) part[(((int64_t)z * 4 + ab) * cout_p + co) * cin_p + ci] = acc[ab];
     if (blockIdx.x == 0 && tci == 0) partb[(int64_t)z * cout_p + co] = accb;
-}
-
-// Transposed 2x2 on the matrix cores: for every output parity ab, dW[ab][co][ci] =
-// sum_i G[2i + ab][co] x[i][ci] with the coarse pixels i as the reduction index. Block: 32 x 32
-// channels over its chunk of 8 x 16 coarse tiles, staged transposed in LDS as in k_wgrad3_mfma;
-// wavefront w owns the channel pair (w / 2, w % 2) for the 4 parities.
-__global__ __launch_bounds__(TT) void k_wgradT_mfma(const bf16_t* __restrict__ G, int cout_p,
-                                                    const bf16_t* __restrict__ x, int cin_p, int H, int W,
-                                                    int ntiles, int tpc, float* __restrict__ part,
-                                                    float* __restrict__ partb) {
-    __shared__ __attribute__((aligned(16))) bf16_t gt[4 * WG_CO * WG_GS];
-    __shared__ __attribute__((aligned(16))) bf16_t xt[WG_CI * WG_GS];
-    const int ci0 = blockIdx.x * WG_CI, co0 = blockIdx.y * WG_CO;
-    const int z = blockIdx.z;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int lr = lane & 15, kg = lane >> 4;
-    const int cob = wv >> 1, cib = wv & 1;
-    const int tx_n = (W + 15) / 16, ty_n = (H + 7) / 8;
-    const int per_img = tx_n * ty_n;
-    const int64_t plane = (int64_t)H * W;
-    f32x4_t acc[4];
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[t][r] = 0.f;
-    float accb = 0.f;
-    const int t_beg = z * tpc, t_end = min(ntiles, (z + 1) * tpc);
-    // G at the 4 fine pixels (parity ab) of each of the 128 coarse pixels, and x, staged transposed
-    // by units of 8 coarse pixels x 8 channels as in k_wgrad3_mfma (register transposes, 16-byte
-    // LDS stores, the next tile's loads in flight). Units [0, 256): G (ab, pixel group, part);
-    // [256, 320): x.
-    constexpr int NU = 4 * 16 * 4 + 16 * 4;
-    constexpr int UPT = (NU + TT - 1) / TT;
-    uint4 rg[UPT][8];
-    auto gload = [&](int tile) {
-        const int b = tile / per_img, r = tile - b * per_img;
-        const int ty0 = (r / tx_n) * 8, tx0 = (r % tx_n) * 16;
-#pragma unroll
-        for (int i = 0; i < UPT; ++i) {
-            const int u = threadIdx.x + i * TT;
-            if (u >= NU) break;
-            const int part8 = u & 3;
-            const int pg = (u >> 2) & 15;
-            const int iy = ty0 + (pg >> 1), ix0 = tx0 + 8 * (pg & 1);
-            if (u < 4 * 16 * 4) {
-                const int ab = u >> 6;
-                const int co = co0 + part8 * 8;
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    rg[i][k] = uint4{0, 0, 0, 0};
-                    if (iy < H && ix0 + k < W && co < cout_p) {
-                        const int oy = 2 * iy + (ab >> 1), ox = 2 * (ix0 + k) + (ab & 1);
-                        rg[i][k] = *(const uint4*)(G + ((int64_t)b * 4 * plane + (int64_t)oy * 2 * W + ox) * cout_p + co);
-                    }
-                }
-            } else {
-                const int ci = ci0 + part8 * 8;
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    rg[i][k] = uint4{0, 0, 0, 0};
-                    if (iy < H && ix0 + k < W && ci < cin_p)
-                        rg[i][k] = *(const uint4*)(x + ((int64_t)b * plane + (int64_t)iy * W + ix0 + k) * cin_p + ci);
-                }
-            }
-        }
-    };
-    auto lstore = [&]() {
-#pragma unroll
-        for (int i = 0; i < UPT; ++i) {
-            const int u = threadIdx.x + i * TT;
-            if (u >= NU) break;
-            const int part8 = u & 3;
-            const int pg = (u >> 2) & 15;
-            bf16_t* dst = u < 4 * 16 * 4 ? &gt[((u >> 6) * WG_CO + part8 * 8) * WG_GS + 8 * pg]
-                                         : &xt[(part8 * 8) * WG_GS + 8 * pg];
-            uint4 o[8];
-            wg_transpose8(rg[i], o);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) *(uint4*)(dst + k * WG_GS) = o[k];
-        }
-    };
-    if (t_beg < t_end) gload(t_beg);
-    for (int tile = t_beg; tile < t_end; ++tile) {
-        __syncthreads();   // the previous tile's reads of the LDS are done
-        lstore();
-        __syncthreads();
-        if (tile + 1 < t_end) gload(tile + 1);
-        if (blockIdx.x == 0) {
-            const int co = threadIdx.x >> 3, seg = threadIdx.x & 7;
-#pragma unroll
-            for (int ab = 0; ab < 4; ++ab)
-#pragma unroll
-                for (int k = 0; k < 16; ++k) accb += bf2f(gt[(ab * WG_CO + co) * WG_GS + seg * 16 + k]);
-        }
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const bf16x8_t bb = PolBF16::load(&xt[(cib * 16 + lr) * WG_GS + 32 * s + 8 * kg]);
-#pragma unroll
-            for (int ab = 0; ab < 4; ++ab) {
-                const bf16x8_t a = PolBF16::load(&gt[(ab * WG_CO + cob * 16 + lr) * WG_GS + 32 * s + 8 * kg]);
-                acc[ab] = PolBF16::mma(a, bb, acc[ab]);
-            }
-        }
-    }
-    const int ci = ci0 + cib * 16 + lr;
-    if (ci < cin_p) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int co = co0 + cob * 16 + 4 * kg + r;
-            if (co < cout_p) {
-                float* dst = part + (((int64_t)z * cout_p + co) * cin_p + ci) * 4;
-#pragma unroll
-                for (int ab = 0; ab < 4; ++ab) dst[ab] = acc[ab][r];
-            }
-        }
-    }
-    if (blockIdx.x == 0) {
-        accb += __shfl_xor(accb, 1, 64);
-        accb += __shfl_xor(accb, 2, 64);
-        accb += __shfl_xor(accb, 4, 64);
-        const int co = co0 + (threadIdx.x >> 3);
-        if ((threadIdx.x & 7) == 0 && co < cout_p) partb[(int64_t)z * cout_p + co] = accb;
-    }
 }
 
 // Sum the chunk partials of one layer into the flat FP32 gradient (logical channels).
 // grad[...] = sum over the nchunk partials, in a fixed order: a block covers 32 consecutive
-// outputs; thread group g (of 8) sums the chunks z = g mod 8, and the 8 group sums are added
-// in order g = 0..7.
+// entries of a partial (its order, [tap][co][ci]: the reads are what counts); thread group g (of
+// 8) sums the chunks z = g mod 8, and the 8 group sums are added in order.
 constexpr int WR_OUT = 32, WR_GRP = 8;
 __global__ __launch_bounds__(WR_OUT * WR_GRP) void k_wgrad_reduce(const float* __restrict__ part,
                                                                  const float* __restrict__ partb, int nchunk,
@@ -777,34 +431,35 @@ __global__ __launch_bounds__(WR_OUT * WR_GRP) void k_wgrad_reduce(const float* _
     const int64_t t = (int64_t)blockIdx.x * WR_OUT + o;
     const int taps = ly.kind == L_CONV3 ? 9 : 4;
     const int64_t nw = (int64_t)taps * ly.cin * ly.cout;
-    float a = 0;
+    const float* src = nullptr;
+    int64_t stride = 0, dst = 0;
     if (t < nw) {
-        int co, ci, tap;
-        if (ly.kind == L_CONV3) {         // flat [co][ci][tap]
-            tap = (int)(t % 9);
-            ci = (int)((t / 9) % ly.cin);
-            co = (int)(t / (9 * ly.cin));
-        } else {                          // flat [ci][co][ab]
-            tap = (int)(t % 4);
-            co = (int)((t / 4) % ly.cout);
-            ci = (int)(t / (4 * ly.cout));
-        }
+        const int ci = (int)(t % ly.cin), q = (int)(t / ly.cin);
+        const int co = q % ly.cout, tap = q / ly.cout;
         int cis = ci;                     // stored channel of a concatenated input
         if (ly.cat_cp > 0 && ci >= ly.cat_c) cis = ly.cat_cp + (ci - ly.cat_c);
-        for (int z = g; z < nchunk; z += WR_GRP)
-            a += part[(((int64_t)z * ly.cout_p + co) * ly.cin_p + cis) * taps + tap];
+        src = part + ((int64_t)tap * ly.cout_p + co) * ly.cin_p + cis;
+        stride = (int64_t)taps * ly.cout_p * ly.cin_p;
+        // flat [co][ci][tap] (3x3) or [ci][co][ab] (transposed)
+        dst = ly.w_off + (ly.kind == L_CONV3 ? ((int64_t)co * ly.cin + ci) * 9 + tap
+                                             : ((int64_t)ci * ly.cout + co) * 4 + tap);
     } else if (t < nw + ly.cout) {
-        const int co = (int)(t - nw);
-        for (int z = g; z < nchunk; z += WR_GRP) a += partb[(int64_t)z * ly.cout_p + co];
+        src = partb + (t - nw);
+        stride = ly.cout_p;
+        dst = ly.b_off + (t - nw);
+    }
+    float a = 0;
+    if (src) {
+#pragma unroll 8
+        for (int z = g; z < nchunk; z += WR_GRP) a += src[z * stride];
     }
     red[g][o] = a;
     __syncthreads();
-    if (g == 0 && t < nw + ly.cout) {
+    if (g == 0 && src) {
         float sum = 0;
 #pragma unroll
         for (int k = 0; k < WR_GRP; ++k) sum += red[k][o];
-        if (t < nw) grad[ly.w_off + t] = sum;
-        else grad[ly.b_off + (t - nw)] = sum;
+        grad[dst] = sum;
     }
 }
 
@@ -960,8 +615,8 @@ struct TrainBufs {
     size_t total;
 };
 
-constexpr int WCHUNKS = 64;          // pixel chunks of the scalar weight-gradient kernels
-constexpr int WCHUNKS_MAX = 1024;    // upper bound of the matrix-core and head chunk counts
+constexpr int WCHUNKS = 64;          // pixel chunks of every layer's weight gradient that the scratch holds
+constexpr int WCHUNKS_MAX = 1024;    // upper bound of the weight-gradient and head chunk counts
 
 template <class P>
 static TrainBufs<P> train_layout(const no_net* net, const hz_problem* p, int B, void* base, size_t cap,
@@ -1029,77 +684,60 @@ static TrainBufs<P> train_layout(const no_net* net, const hz_problem* p, int B, 
 // ------------------------------------------------------------------ launch helpers
 
 template <class P>
-static int wgrad_conv3(const Layer& ly, const typename P::T* G, const typename P::T* x0, int c0,
-                       const typename P::T* x1, int c1, int H, int W, int B, TrainBufs<P>& t, float* grad,
-                       hipStream_t s) {
-    const int ntiles = ((W + 15) / 16) * ((H + 7) / 8) * B;
-    int nchunk;
-    if constexpr (std::is_same<P, PolBF16>::value || std::is_same<P, PolF32>::value) {
-        // matrix-core form: about 1024 blocks (512 in BF16, whose blocks prefetch their next tile),
-        // as many chunks as the partial buffer holds
-        const int ctiles = ((ly.cin_p + WG_CI - 1) / WG_CI) * ((ly.cout_p + WG_CO - 1) / WG_CO);
-        const size_t per_chunk = (size_t)9 * ly.cout_p * ly.cin_p;
-        const int nb = std::is_same<P, PolBF16>::value ? 512 : 1024;
-        int want = std::min(512, std::max(1, (nb + ctiles - 1) / ctiles));
-        want = (int)std::min<size_t>((size_t)want, t.wcap / per_chunk);
-        want = std::min(want, (int)std::min<size_t>((size_t)WCHUNKS_MAX, t.bcap / (size_t)ly.cout_p));
-        const int tpc = (ntiles + want - 1) / want;
-        nchunk = (ntiles + tpc - 1) / tpc;
-        dim3 grid((ly.cin_p + WG_CI - 1) / WG_CI, (ly.cout_p + WG_CO - 1) / WG_CO, nchunk);
-        if constexpr (std::is_same<P, PolBF16>::value)
-            hipLaunchKernelGGL(k_wgrad3_mfma, grid, dim3(TT), 0, s, G, ly.cout_p, x0, c0, x1, c1, H, W, ntiles, tpc,
-                               t.wpart, t.wpartb);
-        else
-            hipLaunchKernelGGL(k_wgrad3_mfma_f32, grid, dim3(TT), 0, s, G, ly.cout_p, x0, c0, x1, c1, H, W, ntiles,
-                               tpc, t.wpart, t.wpartb);
-    } else {
-        const int tpc = (ntiles + WCHUNKS - 1) / WCHUNKS;
-        nchunk = (ntiles + tpc - 1) / tpc;
-        dim3 grid((ly.cin_p + 15) / 16, ly.cout_p / 16, nchunk);
-        hipLaunchKernelGGL(k_wgrad3<P>, grid, dim3(TT), 0, s, G, ly.cout_p, x0, c0, x1, c1, H, W, ntiles, tpc,
-                           t.wpart, t.wpartb);
-    }
-    HZ_LAUNCH_CHECK();
-    const int64_t nout = (int64_t)9 * ly.cin * ly.cout + ly.cout;
+static int wgrad_reduce(const Layer& ly, int nchunk, const TrainBufs<P>& t, float* grad, hipStream_t s) {
+    const int64_t nout = (int64_t)(ly.kind == L_CONV3 ? 9 : 4) * ly.cin * ly.cout + ly.cout;
     hipLaunchKernelGGL(k_wgrad_reduce, dim3((unsigned)((nout + WR_OUT - 1) / WR_OUT)), dim3(WR_OUT * WR_GRP), 0, s,
                        t.wpart, t.wpartb, nchunk, ly, grad);
     HZ_LAUNCH_CHECK();
     return HZ_OK;
+}
+
+// chunks that the partial buffers hold
+template <class P>
+static int wgrad_cap(const Layer& ly, int taps, const TrainBufs<P>& t) {
+    const size_t w = t.wcap / ((size_t)taps * ly.cout_p * ly.cin_p), b = t.bcap / (size_t)ly.cout_p;
+    return (int)std::min<size_t>(std::min(w, b), WCHUNKS_MAX);
+}
+
+template <class P>
+static int wgrad_conv3(const Layer& ly, const typename P::T* G, const typename P::T* x0, int c0,
+                       const typename P::T* x1, int c1, int H, int W, int B, TrainBufs<P>& t, float* grad,
+                       hipStream_t s) {
+    if constexpr (std::is_same<P, PolBF16>::value) {
+        WgradArgs<bf16_t> a{G, x0, x1, c0, c0 + c1, ly.cout_p, B, H, W, t.wpart, t.wpartb, 0, 0, 0};
+        HZ_TRY(launch_wgrad3(a, wgrad_cap(ly, 9, t), s));
+        return wgrad_reduce(ly, a.nchunk, t, grad, s);
+    } else {   // about 1024 blocks, as many chunks as the partial buffer holds
+        const int ntiles = ((W + 15) / 16) * ((H + 7) / 8) * B;
+        const int ctiles = ((ly.cin_p + WG_CI - 1) / WG_CI) * ((ly.cout_p + WG_CO - 1) / WG_CO);
+        const int want = std::min(std::min(512, std::max(1, (1024 + ctiles - 1) / ctiles)), wgrad_cap(ly, 9, t));
+        const int tpc = (ntiles + want - 1) / want, nchunk = (ntiles + tpc - 1) / tpc;
+        dim3 grid((ly.cin_p + WG_CI - 1) / WG_CI, (ly.cout_p + WG_CO - 1) / WG_CO, nchunk);
+        hipLaunchKernelGGL(k_wgrad3_mfma_f32, grid, dim3(TT), 0, s, G, ly.cout_p, x0, c0, x1, c1, H, W, ntiles, tpc,
+                           t.wpart, t.wpartb);
+        HZ_LAUNCH_CHECK();
+        return wgrad_reduce(ly, nchunk, t, grad, s);
+    }
 }
 
 template <class P>
 static int wgrad_convT(const Layer& ly, const typename P::T* G, const typename P::T* x, int H, int W, int B,
                        TrainBufs<P>& t, float* grad, hipStream_t s) {
-    int nchunk;
     if constexpr (std::is_same<P, PolBF16>::value) {
-        const int ntiles = ((W + 15) / 16) * ((H + 7) / 8) * B;
-        const int ctiles = ((ly.cin_p + WG_CI - 1) / WG_CI) * ((ly.cout_p + WG_CO - 1) / WG_CO);
-        const size_t per_chunk = (size_t)4 * ly.cout_p * ly.cin_p;
-        int want = std::min(512, std::max(1, (1024 + ctiles - 1) / ctiles));
-        want = (int)std::min<size_t>((size_t)want, t.wcap / per_chunk);
-        want = std::min(want, (int)std::min<size_t>((size_t)WCHUNKS_MAX, t.bcap / (size_t)ly.cout_p));
-        const int tpc = (ntiles + want - 1) / want;
-        nchunk = (ntiles + tpc - 1) / tpc;
-        dim3 grid((ly.cin_p + WG_CI - 1) / WG_CI, (ly.cout_p + WG_CO - 1) / WG_CO, nchunk);
-        hipLaunchKernelGGL(k_wgradT_mfma, grid, dim3(TT), 0, s, G, ly.cout_p, x, ly.cin_p, H, W, ntiles, tpc,
-                           t.wpart, t.wpartb);
+        WgradArgs<bf16_t> a{G, x, nullptr, ly.cin_p, ly.cin_p, ly.cout_p, B, H, W, t.wpart, t.wpartb, 0, 0, 0};
+        HZ_TRY(launch_wgradT(a, wgrad_cap(ly, 4, t), s));
+        return wgrad_reduce(ly, a.nchunk, t, grad, s);
     } else {
         const int ntiles = ((W + 7) / 8) * ((H + 7) / 8) * B;
-        const int tpc = (ntiles + WCHUNKS - 1) / WCHUNKS;
-        nchunk = (ntiles + tpc - 1) / tpc;
+        const int tpc = (ntiles + WCHUNKS - 1) / WCHUNKS, nchunk = (ntiles + tpc - 1) / tpc;
         dim3 grid(ly.cin_p / 16, ly.cout_p / 16, nchunk);
         hipLaunchKernelGGL(k_wgradT<P>, grid, dim3(TT), 0, s, G, ly.cout_p, x, ly.cin_p, H, W, ntiles, tpc,
                            t.wpart, t.wpartb);
+        HZ_LAUNCH_CHECK();
+        return wgrad_reduce(ly, nchunk, t, grad, s);
     }
-    HZ_LAUNCH_CHECK();
-    const int64_t nout = (int64_t)4 * ly.cin * ly.cout + ly.cout;
-    hipLaunchKernelGGL(k_wgrad_reduce, dim3((unsigned)((nout + WR_OUT - 1) / WR_OUT)), dim3(WR_OUT * WR_GRP), 0, s,
-                       t.wpart, t.wpartb, nchunk, ly, grad);
-    HZ_LAUNCH_CHECK();
-    return HZ_OK;
 }
 
-// data gradient of a 3x3 layer: y0 (channels [0, split) or all) and y1 (rest), masks optional
 template <class P>
 static int dgrad_conv3(const no_net* net, const Layer& ly, const typename P::T* G, int H, int W, int B,
                        typename P::T* y0, typename P::T* y1, const typename P::T* mask0, const typename P::T* mask1,
