@@ -233,191 +233,6 @@ __global__ void k_head_reduce(const float* __restrict__ part, int nchunk, int ci
 
 // ------------------------------------------------------------------ weight gradients
 
-constexpr int WG_CO = 32, WG_CI = 32;
-
-// 3x3 weight gradient in FP32 on the matrix cores (v_mfma_f32_16x16x4_f32: one reduction element
-// per lane, 4 pixels per instruction). Block, tiles, partials and bias sums as in k_wgrad3_mfma;
-// the transposed LDS copies hold FP32 values, and a single copy of the 10 x 18 input patch serves
-// every dx since a lane reads one value. Row pitches of 130 and 194 floats (2 mod 32) make the 32
-// lanes of a half-wavefront hit 32 distinct banks.
-constexpr int WF_GS = 128 + 2;
-constexpr int WF_XS = 10 * 18 + 14;
-
-__global__ __launch_bounds__(TT) void k_wgrad3_mfma_f32(const float* __restrict__ G, int cout_p,
-                                                        const float* __restrict__ x0, int c0,
-                                                        const float* __restrict__ x1, int c1, int H, int W,
-                                                        int ntiles, int tpc, float* __restrict__ part,
-                                                        float* __restrict__ partb) {
-    __shared__ float gt[WG_CO * WF_GS];
-    __shared__ float xt[WG_CI * WF_XS];
-    const int cin_p = c0 + c1;
-    const int ci0 = blockIdx.x * WG_CI, co0 = blockIdx.y * WG_CO;
-    const int z = blockIdx.z;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int lr = lane & 15, kg = lane >> 4;
-    const int cob = wv >> 1, cib = wv & 1;
-    const int tx_n = (W + 15) / 16, ty_n = (H + 7) / 8;
-    const int per_img = tx_n * ty_n;
-    const int64_t plane = (int64_t)H * W;
-    f32x4_t acc[9];
-#pragma unroll
-    for (int t = 0; t < 9; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[t][r] = 0.f;
-    float accb = 0.f;
-    const int t_beg = z * tpc, t_end = min(ntiles, (z + 1) * tpc);
-    // G tile (128 pixels x 32 channels) and input patch (10 x 18 pixels x 32 channels) as vectors
-    // of 4 channels: a thread's vectors of the next tile are loaded into registers while the
-    // matrix cores work on this one, then written transposed (one value per LDS row)
-    constexpr int NGV = (128 * 8 + TT - 1) / TT, NXV = (180 * 8 + TT - 1) / TT;
-    float4 rgv[NGV], rxv[NXV];
-    auto gload = [&](int tile) {
-        const int b = tile / per_img, r = tile - b * per_img;
-        const int ty0 = (r / tx_n) * 8, tx0 = (r % tx_n) * 16;
-#pragma unroll
-        for (int i = 0; i < NGV; ++i) {
-            const int v = threadIdx.x + i * TT;
-            const int px = v >> 3, part4 = v & 7;
-            const int gy = ty0 + (px >> 4), gx = tx0 + (px & 15);
-            const int co = co0 + part4 * 4;
-            rgv[i] = float4{0.f, 0.f, 0.f, 0.f};
-            if (v < 128 * 8 && gy < H && gx < W && co < cout_p)
-                rgv[i] = *(const float4*)(G + ((int64_t)b * plane + (int64_t)gy * W + gx) * cout_p + co);
-        }
-#pragma unroll
-        for (int i = 0; i < NXV; ++i) {
-            const int v = threadIdx.x + i * TT;
-            const int px = v >> 3, part4 = v & 7;
-            const int py = px / 18, pc = px - py * 18;
-            const int gy = ty0 + py - 1, gx = tx0 + pc - 1;
-            const int ci = ci0 + part4 * 4;
-            rxv[i] = float4{0.f, 0.f, 0.f, 0.f};
-            if (v < 180 * 8 && gy >= 0 && gy < H && gx >= 0 && gx < W && ci < cin_p) {
-                const int64_t pix = (int64_t)b * plane + (int64_t)gy * W + gx;
-                rxv[i] = *(const float4*)(ci < c0 ? x0 + pix * c0 + ci : x1 + pix * c1 + (ci - c0));
-            }
-        }
-    };
-    auto lstore = [&]() {
-#pragma unroll
-        for (int i = 0; i < NGV; ++i) {
-            const int v = threadIdx.x + i * TT;
-            if (v < 128 * 8) {
-                const int px = v >> 3, part4 = v & 7;
-                gt[(part4 * 4 + 0) * WF_GS + px] = rgv[i].x;
-                gt[(part4 * 4 + 1) * WF_GS + px] = rgv[i].y;
-                gt[(part4 * 4 + 2) * WF_GS + px] = rgv[i].z;
-                gt[(part4 * 4 + 3) * WF_GS + px] = rgv[i].w;
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < NXV; ++i) {
-            const int v = threadIdx.x + i * TT;
-            if (v < 180 * 8) {
-                const int px = v >> 3, part4 = v & 7;
-                xt[(part4 * 4 + 0) * WF_XS + px] = rxv[i].x;
-                xt[(part4 * 4 + 1) * WF_XS + px] = rxv[i].y;
-                xt[(part4 * 4 + 2) * WF_XS + px] = rxv[i].z;
-                xt[(part4 * 4 + 3) * WF_XS + px] = rxv[i].w;
-            }
-        }
-    };
-    if (t_beg < t_end) gload(t_beg);
-    for (int tile = t_beg; tile < t_end; ++tile) {
-        __syncthreads();   // the previous tile's reads of the LDS are done
-        lstore();
-        __syncthreads();
-        if (tile + 1 < t_end) gload(tile + 1);
-        if (blockIdx.x == 0) {
-            const int co = threadIdx.x >> 3, seg = threadIdx.x & 7;
-#pragma unroll
-            for (int k = 0; k < 16; ++k) accb += gt[co * WF_GS + seg * 16 + k];
-        }
-        // 32 reduction steps of 4 pixels: lane group kg takes pixel 4 q + kg
-#pragma unroll 4
-        for (int q = 0; q < 32; ++q) {
-            const int p = 4 * q + kg;
-            const int row = p >> 4, col = p & 15;
-            const float a = gt[(cob * 16 + lr) * WF_GS + p];
-            const float* xb = &xt[(cib * 16 + lr) * WF_XS + row * 18 + col];
-#pragma unroll
-            for (int t = 0; t < 9; ++t)
-                acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, xb[(t / 3) * 18 + t % 3], acc[t], 0, 0, 0);
-        }
-    }
-    // lane holds D[co = co0 + 16 cob + 4 kg + r][ci = ci0 + 16 cib + lr] of every tap
-    const int ci = ci0 + cib * 16 + lr;
-    if (ci < cin_p) {
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int co = co0 + cob * 16 + 4 * kg + r;
-            if (co < cout_p) {
-#pragma unroll
-                for (int t = 0; t < 9; ++t) part[(((int64_t)z * 9 + t) * cout_p + co) * cin_p + ci] = acc[t][r];
-            }
-        }
-    }
-    if (blockIdx.x == 0) {
-        accb += __shfl_xor(accb, 1, 64);
-        accb += __shfl_xor(accb, 2, 64);
-        accb += __shfl_xor(accb, 4, 64);
-        const int co = co0 + (threadIdx.x >> 3);
-        if ((threadIdx.x & 7) == 0 && co < cout_p) partb[(int64_t)z * cout_p + co] = accb;
-    }
-}
-
-// Transposed 2x2: dW[ab][co][ci] = sum_i G[2i + ab][co] x[i][ci]; block: ci tile, co tile, chunk of
-// 8 x 8 input tiles.
-template <class P>
-__global__ __launch_bounds__(TT) void k_wgradT(const typename P::T* __restrict__ G, int cout_p,
-                                               const typename P::T* __restrict__ x, int cin_p, int H, int W,
-                                               int ntiles, int tpc, float* __restrict__ part,
-                                               float* __restrict__ partb) {
-    __shared__ float gs[64][4][17];
-    __shared__ float xs[64][17];
-    const int ci0 = blockIdx.x * 16, co0 = blockIdx.y * 16;
-    const int z = blockIdx.z;
-    const int tco = threadIdx.x >> 4, tci = threadIdx.x & 15;
-    const int tx_n = (W + 7) / 8, ty_n = (H + 7) / 8;
-    const int per_img = tx_n * ty_n;
-    float acc[4] = {0, 0, 0, 0}, accb = 0;
-    const int64_t plane = (int64_t)H * W;
-    const int t_end = min(ntiles, (z + 1) * tpc);
-    for (int tile = z * tpc; tile < t_end; ++tile) {
-        const int b = tile / per_img, r = tile - b * per_img;
-        const int ty0 = (r / tx_n) * 8, tx0 = (r % tx_n) * 8;
-        __syncthreads();
-        for (int v = threadIdx.x; v < 64 * 4 * 16; v += TT) {
-            const int c = v & 15, ab = (v >> 4) & 3, px = v >> 6;
-            const int iy = ty0 + (px >> 3), ix = tx0 + (px & 7);
-            float val = 0.f;
-            if (iy < H && ix < W) {
-                const int oy = 2 * iy + (ab >> 1), ox = 2 * ix + (ab & 1);
-                val = (float)P::val(G[((int64_t)b * 4 * plane + (int64_t)oy * 2 * W + ox) * cout_p + co0 + c]);
-            }
-            gs[px][ab][c] = val;
-        }
-        for (int v = threadIdx.x; v < 64 * 16; v += TT) {
-            const int c = v & 15, px = v >> 4;
-            const int iy = ty0 + (px >> 3), ix = tx0 + (px & 7);
-            float val = 0.f;
-            if (iy < H && ix < W) val = (float)P::val(x[((int64_t)b * plane + (int64_t)iy * W + ix) * cin_p + ci0 + c]);
-            xs[px][c] = val;
-        }
-        __syncthreads();
-        for (int px = 0; px < 64; ++px) {
-            const float xv = xs[px][tci];
-#pragma unroll
-            for (int ab = 0; ab < 4; ++ab) acc[ab] += gs[px][ab][tco] * xv;
-            accb += gs[px][0][tco] + gs[px][1][tco] + gs[px][2][tco] + gs[px][3][tco];
-        }
-    }
-    const int co = co0 + tco, ci = ci0 + tci;
-#pragma unroll
-    for (int ab = 0; ab < 4; ++ab) part[(((int64_t)z * 4 + ab) * cout_p + co) * cin_p + ci] = acc[ab];
-    if (blockIdx.x == 0 && tci == 0) partb[(int64_t)z * cout_p + co] = accb;
-}
-
 // Sum the chunk partials of one layer into the flat FP32 gradient (logical channels).
 // grad[...] = sum over the nchunk partials, in a fixed order: a block covers 32 consecutive
 // entries of a partial (its order, [tap][co][ci]: the reads are what counts); thread group g (of
@@ -703,39 +518,17 @@ template <class P>
 static int wgrad_conv3(const Layer& ly, const typename P::T* G, const typename P::T* x0, int c0,
                        const typename P::T* x1, int c1, int H, int W, int B, TrainBufs<P>& t, float* grad,
                        hipStream_t s) {
-    if constexpr (std::is_same<P, PolBF16>::value) {
-        WgradArgs<bf16_t> a{G, x0, x1, c0, c0 + c1, ly.cout_p, B, H, W, t.wpart, t.wpartb, 0, 0, 0};
-        HZ_TRY(launch_wgrad3(a, wgrad_cap(ly, 9, t), s));
-        return wgrad_reduce(ly, a.nchunk, t, grad, s);
-    } else {   // about 1024 blocks, as many chunks as the partial buffer holds
-        const int ntiles = ((W + 15) / 16) * ((H + 7) / 8) * B;
-        const int ctiles = ((ly.cin_p + WG_CI - 1) / WG_CI) * ((ly.cout_p + WG_CO - 1) / WG_CO);
-        const int want = std::min(std::min(512, std::max(1, (1024 + ctiles - 1) / ctiles)), wgrad_cap(ly, 9, t));
-        const int tpc = (ntiles + want - 1) / want, nchunk = (ntiles + tpc - 1) / tpc;
-        dim3 grid((ly.cin_p + WG_CI - 1) / WG_CI, (ly.cout_p + WG_CO - 1) / WG_CO, nchunk);
-        hipLaunchKernelGGL(k_wgrad3_mfma_f32, grid, dim3(TT), 0, s, G, ly.cout_p, x0, c0, x1, c1, H, W, ntiles, tpc,
-                           t.wpart, t.wpartb);
-        HZ_LAUNCH_CHECK();
-        return wgrad_reduce(ly, nchunk, t, grad, s);
-    }
+    WgradArgs<typename P::T> a{G, x0, x1, c0, c0 + c1, ly.cout_p, B, H, W, t.wpart, t.wpartb, 0, 0, 0};
+    HZ_TRY(launch_wgrad3(a, wgrad_cap(ly, 9, t), s));
+    return wgrad_reduce(ly, a.nchunk, t, grad, s);
 }
 
 template <class P>
 static int wgrad_convT(const Layer& ly, const typename P::T* G, const typename P::T* x, int H, int W, int B,
                        TrainBufs<P>& t, float* grad, hipStream_t s) {
-    if constexpr (std::is_same<P, PolBF16>::value) {
-        WgradArgs<bf16_t> a{G, x, nullptr, ly.cin_p, ly.cin_p, ly.cout_p, B, H, W, t.wpart, t.wpartb, 0, 0, 0};
-        HZ_TRY(launch_wgradT(a, wgrad_cap(ly, 4, t), s));
-        return wgrad_reduce(ly, a.nchunk, t, grad, s);
-    } else {
-        const int ntiles = ((W + 7) / 8) * ((H + 7) / 8) * B;
-        const int tpc = (ntiles + WCHUNKS - 1) / WCHUNKS, nchunk = (ntiles + tpc - 1) / tpc;
-        dim3 grid(ly.cin_p / 16, ly.cout_p / 16, nchunk);
-        hipLaunchKernelGGL(k_wgradT<P>, grid, dim3(TT), 0, s, G, ly.cout_p, x, ly.cin_p, H, W, ntiles, tpc,
-                           t.wpart, t.wpartb);
-        HZ_LAUNCH_CHECK();
-        return wgrad_reduce(ly, nchunk, t, grad, s);
-    }
+    WgradArgs<typename P::T> a{G, x, nullptr, ly.cin_p, ly.cin_p, ly.cout_p, B, H, W, t.wpart, t.wpartb, 0, 0, 0};
+    HZ_TRY(launch_wgradT(a, wgrad_cap(ly, 4, t), s));
+    return wgrad_reduce(ly, a.nchunk, t, grad, s);
 }
 
 template <class P>

@@ -16,6 +16,8 @@ struct WgradArgs {
 
 // 3x3 and transposed 2x2 weight gradients into at most cap chunks of partials; sets a.nchunk.
 int launch_wgrad3(WgradArgs<bf16_t>& a, int cap, hipStream_t s);
+int launch_wgrad3(WgradArgs<float>& a, int cap, hipStream_t s);
 int launch_wgradT(WgradArgs<bf16_t>& a, int cap, hipStream_t s);
+int launch_wgradT(WgradArgs<float>& a, int cap, hipStream_t s);
 
 }  // namespace hz

@@ -1,5 +1,5 @@
-// BF16 weight gradients on the matrix cores (FP32 accumulation): products with the pixels as the
-// reduction index,
+// Weight gradients on the matrix cores (FP32 accumulation): products with the pixels as the reduction
+// index,
 //   3x3:            dW[tap][co][ci] = sum_p G[p][co] X[p + tap][ci],   db[co] = sum_p G[p][co]
 //   transposed 2x2: dW[ab][co][ci] = sum_i G[2i + ab][co] x[i][ci],    db[co] = sum_p G[p][co]
 //
@@ -364,6 +364,231 @@ __global__ __launch_bounds__(256, 2) void k_wgradT(const WgradArgs<typename S::T
         }
 }
 
+// ------------------------------------------------------------------ FP32
+//
+// v_mfma_f32_16x16x4_f32 takes one value per lane, 4 pixels x 16 channels: a read of 256 consecutive
+// bytes of the planes above, so nothing is transposed. It adds its 4 products one after the other
+// (fma, in the order of k), which makes every sum below a plain chain over the pixels of the chunk.
+// The matrix cores are what bounds these (32 clocks for 1 K products; 145 TF measured).
+
+constexpr int WF_PX = 64;   // bytes of 16 channels of a pixel
+
+// 3x3. Block: 32 x 32 channels over its chunk of 8 x 16 pixel tiles of the samples, wavefront w the
+// pair (w / 2, w % 2) for all 9 taps; the chain takes a tile's rows in turn and 4 pixels a step. The
+// operands of an input row serve 3 output rows from registers.
+// Measured, batch 32 at 96^2: 32 -> 32 channels 57 -> 55 us, 64 -> 32 107 -> 104 us (105 TF), against tiles
+// transposed in LDS by 4-byte stores; what is left to the 145 TF is whole blocks of an uneven share
+// of the CUs. (Four blocks to a CU, 128 registers, spill the loads in flight: 101 and 149 us.)
+__global__ __launch_bounds__(256, 3) void k_wgrad3_f32(const WgradArgs<float> A) {
+    constexpr int TW = 16, TH = 8, PW = 18, PH = 10, NT = 256;
+    constexpr int PLG = TW * TH * WF_PX + 64, PLX = PW * PH * WF_PX + 64;
+    constexpr int NG = TW * TH * 8 / NT, NX = (PW * PH * 8 + NT - 1) / NT;
+    __shared__ __attribute__((aligned(16))) unsigned char lds[2 * PLG + 2 * PLX];
+    unsigned char* const ldx = lds + 2 * PLG;
+    int z, ct;
+    wg_block(A.nct, A.nchunk, &z, &ct);
+    if (z >= A.nchunk) return;
+    const int nci = (A.cin_p + 31) / 32;
+    const int ci0 = (ct % nci) * 32, co0 = (ct / nci) * 32;
+    const int lane = threadIdx.x & 63, lr = lane & 15, kg = lane >> 4, w = threadIdx.x >> 6;
+    const int cob = w >> 1, cib = w & 1;
+    const int H = A.H, W = A.W;
+    const int tx_n = (W + TW - 1) / TW, per_img = tx_n * ((H + TH - 1) / TH);
+    f32x4_t acc[9];
+#pragma unroll
+    for (int i = 0; i < 9; ++i) acc[i] = WG_ZERO;
+    const int bco = threadIdx.x & 31, bseg = threadIdx.x >> 5;   // bias: one output channel, one row
+    float accb = 0.f;
+
+    float4 rg[NG], rx[NX];
+    auto gload = [&](int tile) {
+        const int b = tile / per_img, r = tile - b * per_img;
+        const int ty0 = (r / tx_n) * TH, tx0 = (r % tx_n) * TW;
+        const int64_t p0 = (int64_t)b * H * W;
+#pragma unroll
+        for (int i = 0; i < NG; ++i) {
+            const int v = threadIdx.x + i * NT, c = co0 + (v & 7) * 4, px = v >> 3;
+            const int y = ty0 + px / TW, x = tx0 + px % TW;
+            rg[i] = float4{0.f, 0.f, 0.f, 0.f};
+            if (y < H && x < W && c < A.cout_p)
+                rg[i] = *(const float4*)(A.G + (p0 + (int64_t)y * W + x) * A.cout_p + c);
+        }
+#pragma unroll
+        for (int i = 0; i < NX; ++i) {
+            const int v = threadIdx.x + i * NT, c = ci0 + (v & 7) * 4, px = v >> 3;
+            const int y = ty0 + px / PW - 1, x = tx0 + px % PW - 1;
+            rx[i] = float4{0.f, 0.f, 0.f, 0.f};
+            if (v < PW * PH * 8 && y >= 0 && y < H && x >= 0 && x < W && c < A.cin_p) {
+                const int64_t pix = p0 + (int64_t)y * W + x;
+                rx[i] = *(const float4*)(c < A.c0 ? A.x0 + pix * A.c0 + c : A.x1 + pix * (A.cin_p - A.c0) + (c - A.c0));
+            }
+        }
+    };
+    auto lstore = [&]() {
+#pragma unroll
+        for (int i = 0; i < NG; ++i) {
+            const int v = threadIdx.x + i * NT, cv = v & 7, px = v >> 3;
+            *(float4*)(lds + (cv >> 2) * PLG + px * WF_PX + (cv & 3) * 16) = rg[i];
+        }
+#pragma unroll
+        for (int i = 0; i < NX; ++i) {
+            const int v = threadIdx.x + i * NT, cv = v & 7, px = v >> 3;
+            if (v < PW * PH * 8) *(float4*)(ldx + (cv >> 2) * PLX + px * WF_PX + (cv & 3) * 16) = rx[i];
+        }
+    };
+    const unsigned char* const lg = lds + cob * PLG + kg * WF_PX + lr * 4;
+    const unsigned char* const lx = ldx + cib * PLX + kg * WF_PX + lr * 4;
+    const unsigned char* const lb = lds + (bco >> 4) * PLG + bseg * TW * WF_PX + (bco & 15) * 4;
+    const int t_beg = z * A.tpc, t_end = min(per_img * A.B, t_beg + A.tpc);
+    if (t_beg < t_end) gload(t_beg);
+    for (int tile = t_beg; tile < t_end; ++tile) {
+        __syncthreads();   // the previous tile's reads of the LDS are done
+        lstore();
+        __syncthreads();
+        if (tile + 1 < t_end) gload(tile + 1);
+        if (ci0 == 0) {
+#pragma unroll
+            for (int k = 0; k < TW; ++k) accb += *(const float*)(lb + k * WF_PX);
+        }
+        float xr[3][3][4];   // [row][dx][4 pixels]
+        auto row = [&](int r) {
+#pragma unroll
+            for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) xr[r % 3][dx][q] = *(const float*)(lx + (r * PW + 4 * q + dx) * WF_PX);
+        };
+        float g[2][4];       // of this row and the next
+        auto grow = [&](int r) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) g[r & 1][q] = *(const float*)(lg + (r * TW + 4 * q) * WF_PX);
+        };
+        row(0);
+        row(1);
+        grow(0);
+#pragma unroll
+        for (int r = 0; r < TH; ++r) {
+            row(r + 2);      // (used last: its reads take the time of the first two rows' products)
+            if (r + 1 < TH) grow(r + 1);
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int t = 6 * h; t < 6 + 3 * h; ++t)
+                        acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(g[r & 1][q], xr[(r + t / 3) % 3][t % 3][q], acc[t],
+                                                                      0, 0, 0);
+        }
+    }
+    // lane holds D[co = 4 kg + r][ci = lr]
+    const int ci = ci0 + cib * 16 + lr;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int co = co0 + cob * 16 + 4 * kg + r;
+        if (ci >= A.cin_p || co >= A.cout_p) continue;
+#pragma unroll
+        for (int t = 0; t < 9; ++t) A.part[(((int64_t)z * 9 + t) * A.cout_p + co) * A.cin_p + ci] = acc[t][r];
+    }
+    if (ci0 == 0) {   // the rows' sums, pairwise
+        float* red = (float*)lds;
+        __syncthreads();
+        red[bseg * 32 + bco] = accb;
+        __syncthreads();
+        if (threadIdx.x < 32 && co0 + bco < A.cout_p) {
+            float s[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) s[k] = red[k * 32 + bco];
+            A.partb[(int64_t)z * A.cout_p + co0 + bco] = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
+        }
+    }
+}
+
+// Transposed 2x2. Block: 16 output x 32 input channels over its chunk of 8 x 8 coarse tiles of the
+// samples, wavefront ab the parity ab: one operand of G and two of x for two products. G is staged by
+// parity. Measured, batch 32: 64 -> 32 channels to 96^2 200 -> 39 us, 256 -> 128 to 24^2 104 -> 35 us, against one
+// thread per channel pair without the matrix cores.
+__global__ __launch_bounds__(256, 4) void k_wgradT_f32(const WgradArgs<float> A) {
+    constexpr int NPX = 64, NT = 256, PL = NPX * WF_PX + 64;
+    constexpr int NG = 4 * NPX * 4 / NT, NX = NPX * 8 / NT;
+    __shared__ __attribute__((aligned(16))) unsigned char lds[6 * PL];   // G [parity], x [16 channels]
+    unsigned char* const ldx = lds + 4 * PL;
+    int z, ct;
+    wg_block(A.nct, A.nchunk, &z, &ct);
+    if (z >= A.nchunk) return;
+    const int nci = (A.cin_p + 31) / 32;
+    const int ci0 = (ct % nci) * 32, co0 = (ct / nci) * 16;
+    const int lane = threadIdx.x & 63, lr = lane & 15, kg = lane >> 4, ab = threadIdx.x >> 6;
+    const int H = A.H, W = A.W;
+    const int tx_n = (W + 7) / 8, per_img = tx_n * ((H + 7) / 8);
+    f32x4_t acc[2] = {WG_ZERO, WG_ZERO}, accb = WG_ZERO;
+    const bool bias = ci0 == 0 && ab == 0;
+
+    float4 rg[NG], rx[NX];
+    auto gload = [&](int tile) {
+        const int b = tile / per_img, r = tile - b * per_img;
+        const int ty0 = (r / tx_n) * 8, tx0 = (r % tx_n) * 8;
+#pragma unroll
+        for (int i = 0; i < NG; ++i) {   // fine pixels of the tile, rows of 16
+            const int v = threadIdx.x + i * NT, c = co0 + (v & 3) * 4, px = v >> 2;
+            const int y = 2 * ty0 + px / 16, x = 2 * tx0 + px % 16;
+            rg[i] = float4{0.f, 0.f, 0.f, 0.f};
+            if (y < 2 * H && x < 2 * W)
+                rg[i] = *(const float4*)(A.G + (((int64_t)b * 2 * H + y) * (2 * W) + x) * A.cout_p + c);
+        }
+#pragma unroll
+        for (int i = 0; i < NX; ++i) {
+            const int v = threadIdx.x + i * NT, c = ci0 + (v & 7) * 4, px = v >> 3;
+            const int y = ty0 + px / 8, x = tx0 + px % 8;
+            rx[i] = float4{0.f, 0.f, 0.f, 0.f};
+            if (y < H && x < W && c < A.cin_p)
+                rx[i] = *(const float4*)(A.x0 + (((int64_t)b * H + y) * W + x) * A.cin_p + c);
+        }
+    };
+    auto lstore = [&]() {
+#pragma unroll
+        for (int i = 0; i < NG; ++i) {
+            const int v = threadIdx.x + i * NT, px = v >> 2, fx = px % 16, fy = px / 16;
+            *(float4*)(lds + ((fy & 1) * 2 + (fx & 1)) * PL + ((fy >> 1) * 8 + (fx >> 1)) * WF_PX + (v & 3) * 16) = rg[i];
+        }
+#pragma unroll
+        for (int i = 0; i < NX; ++i) {
+            const int v = threadIdx.x + i * NT, cv = v & 7, px = v >> 3;
+            *(float4*)(ldx + (cv >> 2) * PL + px * WF_PX + (cv & 3) * 16) = rx[i];
+        }
+    };
+    const int lo = kg * WF_PX + lr * 4;
+    const int t_beg = z * A.tpc, t_end = min(per_img * A.B, t_beg + A.tpc);
+    if (t_beg < t_end) gload(t_beg);
+    for (int tile = t_beg; tile < t_end; ++tile) {
+        __syncthreads();   // the previous tile's reads of the LDS are done
+        lstore();
+        __syncthreads();
+        if (tile + 1 < t_end) gload(tile + 1);
+#pragma unroll
+        for (int q = 0; q < NPX / 4; ++q) {
+            const int o = lo + 4 * q * WF_PX;
+            const float g = *(const float*)(lds + ab * PL + o);
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+                acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(g, *(const float*)(ldx + i * PL + o), acc[i], 0, 0, 0);
+            if (bias) {   // the 4 parities of a coarse pixel, then the chain over those
+                const float s = ((g + *(const float*)(lds + PL + o)) + *(const float*)(lds + 2 * PL + o)) +
+                                *(const float*)(lds + 3 * PL + o);
+                accb = __builtin_amdgcn_mfma_f32_16x16x4f32(s, 1.f, accb, 0, 0, 0);
+            }
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int co = co0 + 4 * kg + r;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int ci = ci0 + i * 16 + lr;
+            if (ci < A.cin_p) A.part[(((int64_t)z * 4 + ab) * A.cout_p + co) * A.cin_p + ci] = acc[i][r];
+        }
+        if (bias && lr == 0) A.partb[(int64_t)z * A.cout_p + co] = accb[r];
+    }
+}
+
 // chunks of ntiles tiles over nct channel tiles: 512 blocks (two per CU) where the tiles allow it, at
 // most cap chunks
 template <class T>
@@ -422,5 +647,28 @@ int convT(WgradArgs<typename S::T>& a, int cap, hipStream_t s) {
 
 int launch_wgrad3(WgradArgs<bf16_t>& a, int cap, hipStream_t s) { return conv3<WgBF16>(a, cap, s); }
 int launch_wgradT(WgradArgs<bf16_t>& a, int cap, hipStream_t s) { return convT<WgBF16>(a, cap, s); }
+
+int launch_wgrad3(WgradArgs<float>& a, int cap, hipStream_t s) {
+    // about 1024 blocks, as many chunks as the partial buffer holds
+    const int ntiles = (a.W + 15) / 16 * ((a.H + 7) / 8) * a.B;
+    a.nct = (a.cin_p + 31) / 32 * ((a.cout_p + 31) / 32);
+    const int want = std::min(std::min(512, (1024 + a.nct - 1) / a.nct), cap);
+    a.tpc = (ntiles + want - 1) / want;
+    a.nchunk = (ntiles + a.tpc - 1) / a.tpc;
+    hipLaunchKernelGGL(k_wgrad3_f32, dim3(wg_grid(a)), dim3(256), 0, s, a);
+    HZ_LAUNCH_CHECK();
+    return HZ_OK;
+}
+
+int launch_wgradT(WgradArgs<float>& a, int cap, hipStream_t s) {
+    // 64 chunks: with 16 x 32 channel tiles 2 blocks per CU and more
+    const int ntiles = (a.W + 7) / 8 * ((a.H + 7) / 8) * a.B, want = std::min(64, cap);
+    a.nct = (a.cin_p + 31) / 32 * (a.cout_p / 16);
+    a.tpc = (ntiles + want - 1) / want;
+    a.nchunk = (ntiles + a.tpc - 1) / a.tpc;
+    hipLaunchKernelGGL(k_wgradT_f32, dim3(wg_grid(a)), dim3(256), 0, s, a);
+    HZ_LAUNCH_CHECK();
+    return HZ_OK;
+}
 
 }  // namespace hz
