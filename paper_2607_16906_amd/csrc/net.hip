@@ -91,21 +91,39 @@ static bool build_layers(const no_arch* a, std::vector<Layer>& L, int64_t& npara
 // The data-gradient packs hold the same values at [8 - tap][ci][co] (3x3) or [tap][ci][co]
 // (transposed 2x2 and the 8x8 layers).
 // One launch covers every layer: the blocks of layer l are [start[l], start[l + 1]).
-__global__ void k_repack(const float* __restrict__ theta, const Layer* __restrict__ layers,
-                         const int64_t* __restrict__ start, int nl, bf16_t* __restrict__ wb,
-                         float* __restrict__ wf, double* __restrict__ wd, float* __restrict__ bf,
-                         double* __restrict__ bd, bf16_t* __restrict__ tb, float* __restrict__ tf,
-                         double* __restrict__ td, bf16_t* __restrict__ sb, bf16_t* __restrict__ stb,
-                         float* __restrict__ sf, float* __restrict__ stf) {
+//
+// A training step repacks after every update, and the stores are the cost: some 50 bytes per
+// parameter in ten orders. A block owns 32 x 32 channels of a few taps, read once into LDS, and stores
+// them input channels first, then output channels first, so that the 64- to 256-byte runs of every
+// order (and the 1 KB operands of the streamed packs) are completed by one block, in one XCD's L2.
+// Measured with 1.93 M parameters: 67 -> 24 us, against one thread per entry of the first order.
+constexpr int RP = 32, RP_TAPS = 8;
+__host__ __device__ inline int repack_taps(int taps) { return taps == 9 ? 3 : taps == 64 ? RP_TAPS : taps; }   // of a block
+
+__global__ __launch_bounds__(256) void k_repack(const float* __restrict__ theta, const Layer* __restrict__ layers,
+                                                const int64_t* __restrict__ start, int nl, bf16_t* __restrict__ wb,
+                                                float* __restrict__ wf, double* __restrict__ wd,
+                                                float* __restrict__ bf, double* __restrict__ bd,
+                                                bf16_t* __restrict__ tb, float* __restrict__ tf,
+                                                double* __restrict__ td, bf16_t* __restrict__ sb,
+                                                bf16_t* __restrict__ stb, float* __restrict__ sf,
+                                                float* __restrict__ stf) {
+    __shared__ float sm[RP_TAPS][RP][RP + 1];   // [tap][co][ci]
     int l = 0;
     while (l + 1 < nl && (int64_t)blockIdx.x >= start[l + 1]) ++l;
     const Layer ly = layers[l];
-    const int64_t idx = ((int64_t)blockIdx.x - start[l]) * blockDim.x + threadIdx.x;
-    if (idx < ly.pk_len) {
-        const int cis = (int)(idx % ly.cin_p);      // stored input channel
-        const int64_t r = idx / ly.cin_p;
-        const int co = (int)(r % ly.cout_p);
-        const int tap = (int)(r / ly.cout_p);
+    const int taps = (int)(ly.pk_len / ((int64_t)ly.cin_p * ly.cout_p));
+    const int tg = repack_taps(taps);
+    const int nci = (ly.cin_p + RP - 1) / RP, nco = (ly.cout_p + RP - 1) / RP;
+    int q = (int)((int64_t)blockIdx.x - start[l]);
+    const int ci0 = q % nci * RP;
+    q /= nci;
+    const int co0 = q % nco * RP, tap0 = q / nco * tg;
+    const bool t_flat = ly.kind == L_CONVT2 || ly.kind == L_UP8;   // [cin][cout][taps], else [cout][cin][taps]
+    for (int i = threadIdx.x; i < RP * RP * tg; i += 256) {
+        const int tap = i % tg, in = i / tg % RP, out = i / (tg * RP);
+        const int cc = t_flat ? out : in, oc = t_flat ? in : out;
+        const int cis = ci0 + cc, co = co0 + oc;
         // logical input channel; a concatenated input keeps each part's padding
         int ci = cis;
         bool live = cis < ly.cin;
@@ -118,61 +136,63 @@ __global__ void k_repack(const float* __restrict__ theta, const Layer* __restric
             }
         }
         float v = 0.0f;
-        if (live && co < ly.cout) {
-            if (ly.kind == L_CONV3)        // [cout][cin][3][3]
-                v = theta[ly.w_off + ((int64_t)co * ly.cin + ci) * 9 + tap];
-            else if (ly.kind == L_CONVT2)  // [cin][cout][2][2]
-                v = theta[ly.w_off + ((int64_t)ci * ly.cout + co) * 4 + tap];
-            else if (ly.kind == L_DOWN8)   // [cout][cin][8][8]
-                v = theta[ly.w_off + ((int64_t)co * ly.cin + ci) * 64 + tap];
-            else if (ly.kind == L_UP8)     // [cin][cout][8][8]
-                v = theta[ly.w_off + ((int64_t)ci * ly.cout + co) * 64 + tap];
-            else                           // [cout][cin][1][1]
-                v = theta[ly.w_off + (int64_t)co * ly.cin + ci];
+        if (live && co < ly.cout)
+            v = theta[ly.w_off + (t_flat ? (int64_t)ci * ly.cout + co : (int64_t)co * ly.cin + ci) * taps + tap0 + tap];
+        sm[tap][oc][cc] = v;
+    }
+    __syncthreads();
+    const bool fwd = ly.kind == L_CONV3 ? conv3s_layer_ok(ly.cat_cp ? ly.cat_cp : ly.cin_p,
+                                                          ly.cat_cp ? ly.cin_p - ly.cat_cp : 0, ly.cout_p)
+                                        : ly.kind == L_CONVT2 && convT2s_layer_ok<PolBF16>(ly.cin_p, ly.cout_p, false);
+    const bool bwd = ly.kind == L_CONV3 ? conv3s_layer_ok(ly.cout_p, 0, ly.cin_p)
+                                        : ly.kind == L_CONVT2 && convT2s_layer_ok<PolBF16>(ly.cout_p, ly.cin_p, true);
+    for (int i = threadIdx.x; i < RP * RP * tg; i += 256) {   // [tap][co][ci]
+        const int cis = ci0 + i % RP, co = co0 + i / RP % RP, k = i / (RP * RP), tap = tap0 + k;
+        if (cis >= ly.cin_p || co >= ly.cout_p) continue;
+        const float v = sm[k][co - co0][cis - ci0];
+        const int64_t j = ly.pk_off + ((int64_t)tap * ly.cout_p + co) * ly.cin_p + cis;
+        wb[j] = f2bf(v);
+        wf[j] = v;
+        wd[j] = (double)v;
+        if (fwd) {
+            const bool c3 = ly.kind == L_CONV3;
+            sb[ly.pk_off + (c3 ? conv3s_index<bf16_t>(tap, co, cis, ly.cout_p)
+                               : convT2s_index<bf16_t>(tap, cis, co, ly.cin_p, ly.cout_p, false))] = f2bf(v);
+            sf[ly.pk_off + (c3 ? conv3s_index<float>(tap, co, cis, ly.cout_p)
+                               : convT2s_index<float>(tap, cis, co, ly.cin_p, ly.cout_p, false))] = v;
         }
-        wb[ly.pk_off + idx] = f2bf(v);
-        wf[ly.pk_off + idx] = v;
-        wd[ly.pk_off + idx] = (double)v;
-        if (ly.kind != L_CONV1) {
+    }
+    if (ly.kind != L_CONV1)
+        for (int i = threadIdx.x; i < RP * RP * tg; i += 256) {   // [tap][ci][co]
+            const int co = co0 + i % RP, cis = ci0 + i / RP % RP, k = i / (RP * RP), tap = tap0 + k;
+            if (cis >= ly.cin_p || co >= ly.cout_p) continue;
+            const float v = sm[k][co - co0][cis - ci0];
             // data-gradient pack [tap][cin_p][cout_p]: flipped taps for the 3x3 layers; for the 8x8
             // layers the same taps, which makes each one's data gradient the opposite 8x8 form
             const int tt = ly.kind == L_CONV3 ? 8 - tap : tap;
-            const int64_t j = ((int64_t)tt * ly.cin_p + cis) * ly.cout_p + co;
-            tb[ly.pk_off + j] = f2bf(v);
-            tf[ly.pk_off + j] = v;
-            td[ly.pk_off + j] = (double)v;
-        }
-        if (ly.kind == L_CONVT2) {
-            if (convT2s_layer_ok<PolBF16>(ly.cin_p, ly.cout_p, false)) {
-                sb[ly.pk_off + convT2s_index<bf16_t>(tap, cis, co, ly.cin_p, ly.cout_p, false)] = f2bf(v);
-                sf[ly.pk_off + convT2s_index<float>(tap, cis, co, ly.cin_p, ly.cout_p, false)] = v;
-            }
-            if (convT2s_layer_ok<PolBF16>(ly.cout_p, ly.cin_p, true)) {
-                stb[ly.pk_off + convT2s_index<bf16_t>(tap, cis, co, ly.cin_p, ly.cout_p, true)] = f2bf(v);
-                stf[ly.pk_off + convT2s_index<float>(tap, cis, co, ly.cin_p, ly.cout_p, true)] = v;
-            }
-        }
-        if (ly.kind == L_CONV3) {
-            const bool fwd = conv3s_layer_ok(ly.cat_cp ? ly.cat_cp : ly.cin_p, ly.cat_cp ? ly.cin_p - ly.cat_cp : 0, ly.cout_p);
-            const bool bwd = conv3s_layer_ok(ly.cout_p, 0, ly.cin_p);
-            if (fwd) {
-                sb[ly.pk_off + conv3s_index<bf16_t>(tap, co, cis, ly.cout_p)] = f2bf(v);
-                sf[ly.pk_off + conv3s_index<float>(tap, co, cis, ly.cout_p)] = v;
-            }
+            const int64_t j = ly.pk_off + ((int64_t)tt * ly.cin_p + cis) * ly.cout_p + co;
+            tb[j] = f2bf(v);
+            tf[j] = v;
+            td[j] = (double)v;
             if (bwd) {
-                stb[ly.pk_off + conv3s_index<bf16_t>(8 - tap, cis, co, ly.cin_p)] = f2bf(v);
-                stf[ly.pk_off + conv3s_index<float>(8 - tap, cis, co, ly.cin_p)] = v;
+                const bool c3 = ly.kind == L_CONV3;
+                stb[ly.pk_off + (c3 ? conv3s_index<bf16_t>(8 - tap, cis, co, ly.cin_p)
+                                    : convT2s_index<bf16_t>(tap, cis, co, ly.cin_p, ly.cout_p, true))] = f2bf(v);
+                stf[ly.pk_off + (c3 ? conv3s_index<float>(8 - tap, cis, co, ly.cin_p)
+                                    : convT2s_index<float>(tap, cis, co, ly.cin_p, ly.cout_p, true))] = v;
             }
         }
-    }
-    if (idx < ly.cout_p) {
-        const float b = idx < ly.cout ? theta[ly.b_off + idx] : 0.0f;
-        bf[ly.bias_off + idx] = b;
-        bd[ly.bias_off + idx] = (double)b;
-    }
-    if (idx == 0 && ly.a_off >= 0) {   // PReLU slope after the bias
-        bf[ly.bias_off + ly.cout_p] = theta[ly.a_off];
-        bd[ly.bias_off + ly.cout_p] = (double)theta[ly.a_off];
+    if (ci0 == 0 && tap0 == 0) {
+        const int co = co0 + threadIdx.x;
+        if (threadIdx.x < RP && co < ly.cout_p) {
+            const float b = co < ly.cout ? theta[ly.b_off + co] : 0.0f;
+            bf[ly.bias_off + co] = b;
+            bd[ly.bias_off + co] = (double)b;
+        }
+        if (co0 == 0 && threadIdx.x == 0 && ly.a_off >= 0) {   // PReLU slope after the bias
+            bf[ly.bias_off + ly.cout_p] = theta[ly.a_off];
+            bd[ly.bias_off + ly.cout_p] = (double)theta[ly.a_off];
+        }
     }
 }
 
@@ -624,8 +644,9 @@ extern "C" int no_net_create(const no_arch* a, const float* theta, void* stream,
     std::vector<int64_t> start(nl + 1, 0);
     for (size_t l = 0; l < nl; ++l) {
         const Layer& ly = net->layers[l];
-        const int64_t n = std::max<int64_t>(ly.pk_len, ly.cout_p);
-        start[l + 1] = start[l] + (n + 255) / 256;
+        const int taps = (int)(ly.pk_len / ((int64_t)ly.cin_p * ly.cout_p));
+        start[l + 1] = start[l] + (int64_t)((ly.cin_p + RP - 1) / RP) * ((ly.cout_p + RP - 1) / RP) *
+                                      (taps / repack_taps(taps));
     }
     net->repack_blocks = start[nl];
     hipStream_t s = (hipStream_t)stream;

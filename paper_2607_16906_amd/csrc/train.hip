@@ -1190,15 +1190,15 @@ __global__ void k_sqnorm_part(const float* __restrict__ g, int64_t n, double* __
 __global__ void k_adam(float* __restrict__ th, float* __restrict__ m, float* __restrict__ v,
                        const float* __restrict__ g, int64_t n, const double* __restrict__ part, int nparts, int step,
                        float lr, float b1, float b2, float eps, float clip) {
-    __shared__ double scale;
-    if (threadIdx.x == 0) {
-        double a = 0;
-        for (int q = 0; q < nparts; ++q) a += part[q];
-        const double nrm = sqrt(a);
-        scale = (clip > 0 && nrm > clip) ? clip / nrm : 1.0;
-    }
+    // every block adds the norm's partials itself, side by side (one thread after the other: 30 us)
+    __shared__ double red[4];
+    double a = 0;
+    for (int q = threadIdx.x; q < nparts; q += 256) a += part[q];
+    a = wave_sum(a);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = a;
     __syncthreads();
-    const float sc = (float)scale;
+    const double nrm = sqrt((red[0] + red[1]) + (red[2] + red[3]));
+    const float sc = (float)((clip > 0 && nrm > clip) ? clip / nrm : 1.0);
     const float c1 = 1.0f - powf(b1, (float)step), c2 = 1.0f - powf(b2, (float)step);
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const float gi = g[i] * sc;
@@ -1271,7 +1271,7 @@ extern "C" int no_adam_step(no_net* net, float* theta, float* m, float* v, const
     hipStream_t s = (hipStream_t)stream;
     double* part = (double*)ws;
     hipLaunchKernelGGL(k_sqnorm_part, dim3(ADAM_BLOCKS), dim3(256), 0, s, grad, net->nparam, part);
-    hipLaunchKernelGGL(k_adam, dim3(ADAM_BLOCKS), dim3(256), 0, s, theta, m, v, grad, net->nparam, part, ADAM_BLOCKS,
+    hipLaunchKernelGGL(k_adam, dim3(2 * ADAM_BLOCKS), dim3(256), 0, s, theta, m, v, grad, net->nparam, part, ADAM_BLOCKS,
                        step, lr, b1, b2, eps, clip);
     HZ_LAUNCH_CHECK();
     return no_net_set_weights(net, theta, stream);
