@@ -86,16 +86,10 @@ __global__ __launch_bounds__(256) void kb_resid(const TileJob* __restrict__ jobs
     const int64_t p0 = (int64_t)jb.c0 * d.per;                \
     const int64_t p1 = min(d.n, p0 + d.per);
 
-template <typename C>
-__global__ __launch_bounds__(KT) void kb_norm(const TileJob* __restrict__ jobs, const KDesc* __restrict__ kd,
-                                              int what, int col) {
+// ||b||^2 into part slot 0 (b is FP64)
+__global__ __launch_bounds__(KT) void kb_norm(const TileJob* __restrict__ jobs, const KDesc* __restrict__ kd) {
     KB_RANGE
-    if (what == 0) {   // ||b||^2 into part slot 0 (b is FP64)
-        norm_body((const double2*)d.b, p0, p1, d.part + (int64_t)jb.c0 * d.ldp);
-    } else {           // ||v_col||^2 into the network-scale partials
-        if (d.st->stop) return;
-        norm_body((const C*)d.V + (int64_t)col * d.n, p0, p1, d.npart + jb.c0);
-    }
+    norm_body((const double2*)d.b, p0, p1, d.part + (int64_t)jb.c0 * d.ldp);
 }
 
 template <typename C>
@@ -140,9 +134,10 @@ __global__ void kb_arnoldi_finish(const KDesc* __restrict__ kd, const int* __res
     arnoldi_finish_body(d.st, d.R, d.cs, d.sn, d.g, d.h1, d.h2, d.part, d.nblk, d.ldp, j, d.hist);
 }
 
+// v_col scaled to norm 1; net: its ||v_col||^2 as stored, for the network's input scale
 template <typename C>
 __global__ __launch_bounds__(KT) void kb_scale(const TileJob* __restrict__ jobs, const KDesc* __restrict__ kd,
-                                               int col) {
+                                               int col, int net) {
     KB_RANGE
     if (d.st->stop) return;
     C* v = (C*)d.V + (int64_t)col * d.n;
@@ -151,6 +146,9 @@ __global__ __launch_bounds__(KT) void kb_scale(const TileJob* __restrict__ jobs,
         const C a = v[p];
         v[p] = from_d2<C>(double2{a.x * s, a.y * s});
     }
+    if (!net) return;
+    __syncthreads();   // the sum reads points written by other threads of the block
+    norm_body((const C*)v, p0, p1, d.npart + jb.c0);
 }
 
 __global__ void kb_init_state(const KDesc* __restrict__ kd, const int* __restrict__ act, double tol, int m,
@@ -177,6 +175,7 @@ __global__ __launch_bounds__(KT) void kb_xupdate(const TileJob* __restrict__ job
     const C* Z = (const C*)d.Z;
     for (int64_t p = p0 + threadIdx.x; p < p1; p += KT) {
         double2 a = d.x[p];
+#pragma unroll 8
         for (int i = 0; i < k; ++i) {
             const C z = Z[(int64_t)i * d.n + p];
             const double2 yi = d.y[i];
@@ -188,7 +187,8 @@ __global__ __launch_bounds__(KT) void kb_xupdate(const TileJob* __restrict__ job
 }
 
 template <typename C>
-__global__ __launch_bounds__(KT) void kb_cast_scale(const TileJob* __restrict__ jobs, const KDesc* __restrict__ kd) {
+__global__ __launch_bounds__(KT) void kb_cast_scale(const TileJob* __restrict__ jobs, const KDesc* __restrict__ kd,
+                                                    int net) {
     KB_RANGE
     if (d.st->stop) return;
     const double s = d.st->inv_beta;
@@ -197,9 +197,12 @@ __global__ __launch_bounds__(KT) void kb_cast_scale(const TileJob* __restrict__ 
         const double2 a = d.r64[p];
         v[p] = from_d2<C>(double2{a.x * s, a.y * s});
     }
+    if (!net) return;
+    __syncthreads();
+    norm_body((const C*)v, p0, p1, d.npart + jb.c0);
 }
 
-// network input scale s = ||v|| / sqrt(n)
+// network input scale s = ||v|| / sqrt(n) (a launch of 5 us; added by every packing block: 7 us more there)
 __global__ void kb_scale_factor(const KDesc* __restrict__ kd, const int* __restrict__ act) {
     const KDesc& d = kd[act[blockIdx.x]];
     if (d.st->stop) return;
@@ -635,7 +638,6 @@ static int net_step(const BatchPlan<P>& B, const HostTables<P>& h, const no_net*
     const BatchTables& t = B.t;
     const int nact = (int)h.act.size();
     const int nv = (int)h.vjobs.size();
-    hipLaunchKernelGGL((kb_norm<C>), dim3(nv), dim3(KT), 0, s, t.vjobs, t.kd, 1, col);
     hipLaunchKernelGGL(kb_scale_factor, dim3(nact), dim3(64), 0, s, t.kd, t.act);
     hipLaunchKernelGGL((kb_pack<P, C>), dim3((unsigned)h.pjobs.size()), dim3(256), 0, s, t.pjobs, t.kd, col,
                        net->a.in_ch);
@@ -723,14 +725,14 @@ static int cycle_launches(const BatchPlan<P>& B, const HostTables<P>& h, const n
         hipLaunchKernelGGL(kb_finalize, dim3(nact, j + 1), dim3(KT), 0, s, t.kd, t.act, 2);
         hipLaunchKernelGGL((kb_update<C, 2>), dim3(nv), dim3(KT), 0, s, t.vjobs, t.kd, j + 1);
         hipLaunchKernelGGL(kb_arnoldi_finish, dim3(nact), dim3(64), 0, s, t.kd, t.act, j);
-        hipLaunchKernelGGL((kb_scale<C>), dim3(nv), dim3(KT), 0, s, t.vjobs, t.kd, j + 1);
+        hipLaunchKernelGGL((kb_scale<C>), dim3(nv), dim3(KT), 0, s, t.vjobs, t.kd, j + 1, net ? 1 : 0);
         HZ_LAUNCH_CHECK();
     }
     hipLaunchKernelGGL(kb_backsolve, dim3(nact), dim3(64), 0, s, t.kd, t.act);
     hipLaunchKernelGGL((kb_xupdate<C>), dim3(nv), dim3(KT), 0, s, t.vjobs, t.kd);
     hipLaunchKernelGGL(kb_resid, dim3(nst), dim3(256), 0, s, t.stjobs, t.kd);
     hipLaunchKernelGGL(kb_cycle_start, dim3(nact), dim3(64), 0, s, t.kd, t.act, m);
-    hipLaunchKernelGGL((kb_cast_scale<C>), dim3(nv), dim3(KT), 0, s, t.vjobs, t.kd);
+    hipLaunchKernelGGL((kb_cast_scale<C>), dim3(nv), dim3(KT), 0, s, t.vjobs, t.kd, net ? 1 : 0);
     HZ_LAUNCH_CHECK();
     return HZ_OK;
 }
@@ -771,11 +773,11 @@ static int solve_batched(int nsys, const hz_problem* const* probs, const no_net*
         if ((rc = upload_tables<P>(B, h, s)) != HZ_OK) break;
         const BatchTables& t = B.t;
         const int nv = (int)h.vjobs.size(), nst = (int)h.stjobs.size();
-        hipLaunchKernelGGL((kb_norm<C>), dim3(nv), dim3(KT), 0, s, t.vjobs, t.kd, 0, 0);
+        hipLaunchKernelGGL(kb_norm, dim3(nv), dim3(KT), 0, s, t.vjobs, t.kd);
         hipLaunchKernelGGL(kb_init_state, dim3(nsys), dim3(64), 0, s, t.kd, t.act, o->tol, o->m, std::max(o->maxit, 1));
         hipLaunchKernelGGL(kb_resid, dim3(nst), dim3(256), 0, s, t.stjobs, t.kd);
         hipLaunchKernelGGL(kb_cycle_start, dim3(nsys), dim3(64), 0, s, t.kd, t.act, o->m);
-        hipLaunchKernelGGL((kb_cast_scale<C>), dim3(nv), dim3(KT), 0, s, t.vjobs, t.kd);
+        hipLaunchKernelGGL((kb_cast_scale<C>), dim3(nv), dim3(KT), 0, s, t.vjobs, t.kd, net ? 1 : 0);
         if (hipGetLastError() != hipSuccess) {
             rc = HZ_ERR_HIP;
             break;

@@ -115,7 +115,7 @@ __global__ __launch_bounds__(KT) void k_stencil_dots(const C* __restrict__ z, St
 }
 
 constexpr int UPD_REG = 32;   // vectors held in registers by the single-pass first update
-constexpr int UPD_SPLIT4 = 24; // up to this many vectors pass 2 splits them over 4 wavefronts
+constexpr int UPD_SPLIT4 = 24; // up to this many FP32 vectors pass 2 splits them over 4 wavefronts
 
 // w = A z and the pass-1 sums for FP32 vectors read as point pairs (even row length, 16-byte
 // aligned vectors, even stride), with the basis split over the NW wavefronts of the block
@@ -304,6 +304,79 @@ __global__ __launch_bounds__(NW * 64) void k_upd1_split(const float2* __restrict
         double (&sr)[IC] = *reinterpret_cast<double (*)[IC]>(&ar[g0]);
         double (&si)[IC] = *reinterpret_cast<double (*)[IC]>(&ai[g0]);
         wave_store8(sr, si, mine + g0, cnt - g0);
+    }
+}
+
+// Pass 2 with one point per thread (ranges of KT points) and up to UPD_REG vectors, 8 at a time: w' from
+// all of them in order, then the sums, the last 8 from registers and the others read again (from the
+// caches). The same sums as k_update's register form, whose straight code for 32 vectors (27 KB, 336
+// registers) takes 20 us whatever nv; this 11.7 us for 25 to 30 vectors of 296^2 points.
+template <typename C>
+__global__ __launch_bounds__(KT) void k_upd1_point(const C* __restrict__ V, int64_t ldv, int nv,
+                                                   const double2* __restrict__ h, C* __restrict__ w, int64_t n,
+                                                   double2* __restrict__ part, int ldp,
+                                                   const int* __restrict__ skip) {
+    const int skipped = skip ? *skip : 0;   // tested after the first loads are issued
+    const int64_t p = blockIdx.x * (int64_t)KT + threadIdx.x;
+    const bool live = p < n;
+    const C* __restrict__ vp = V + (live ? p : n - 1);
+    const C w0 = w[live ? p : n - 1];
+    C v[IC], nx[IC];
+    auto load = [&](C (&d)[IC], int i0) {
+#pragma unroll
+        for (int q = 0; q < IC; ++q)
+            if (i0 + q < nv) d[q] = vp[(int64_t)(i0 + q) * ldv];
+    };
+    load(v, 0);
+    asm volatile("" ::"v"(w0.x));
+    if (skipped) return;
+    double ax = w0.x, ay = w0.y;
+    const int last = (nv - 1) / IC * IC;
+#pragma unroll 1
+    for (int i0 = 0; i0 <= last; i0 += IC) {
+        if (i0) {
+#pragma unroll
+            for (int q = 0; q < IC; ++q) v[q] = nx[q];
+        }
+        if (i0 < last) load(nx, i0 + IC);
+#pragma unroll
+        for (int q = 0; q < IC; ++q)
+            if (i0 + q < nv) {
+                const double2 hi = h[i0 + q];
+                ax -= (double)v[q].x * hi.x - (double)v[q].y * hi.y;
+                ay -= (double)v[q].x * hi.y + (double)v[q].y * hi.x;
+            }
+    }
+    const C wp = from_d2<C>(double2{ax, ay});
+    if (live) w[p] = wp;
+    __shared__ double red[KT / 64][2 * UPD_REG];
+    const int wv = threadIdx.x >> 6;
+#pragma unroll 1
+    for (int i0 = last; i0 >= 0; i0 -= IC) {
+        if (i0 < last) {
+#pragma unroll
+            for (int q = 0; q < IC; ++q) v[q] = nx[q];
+        }
+        if (i0) load(nx, i0 - IC);
+        double ar[IC], ai[IC];
+#pragma unroll
+        for (int q = 0; q < IC; ++q) {
+            ar[q] = ai[q] = 0.0;
+            if (i0 + q < nv && live) {
+                ar[q] += (double)v[q].x * wp.x + (double)v[q].y * wp.y;
+                ai[q] += (double)v[q].x * wp.y - (double)v[q].y * wp.x;
+            }
+        }
+        int idx;
+        const double s = wave_reduce8(ar, ai, &idx);
+        if ((threadIdx.x & 3) == 0) red[wv][2 * i0 + idx] = s;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2 * nv) {
+        double t = 0;
+#pragma unroll
+        for (int k = 0; k < KT / 64; ++k) t += red[k][threadIdx.x];
+        ((double*)(part + (int64_t)blockIdx.x * ldp))[threadIdx.x] = t;
     }
 }
 
@@ -660,13 +733,18 @@ int launch_update(bool c128, const void* V, int64_t ldv, int nv, const double2* 
 #define HZ_UPD(C, M)                                                                                   \
     hipLaunchKernelGGL((k_update<C, M>), dim3(sp.nblk), dim3(KT), 0, s, (const C*)V, ldv, nv, h, (C*)w, n, \
                        sp.per_block, part, ldp, skip)
+#define HZ_UPDP(C)                                                                                       \
+    hipLaunchKernelGGL(k_upd1_point<C>, dim3(sp.nblk), dim3(KT), 0, s, (const C*)V, ldv, nv, h, (C*)w, n, part, \
+                       ldp, skip)
+    const bool point = mode == 1 && nv <= UPD_REG && sp.per_block == KT;   // else k_update's loop over points
     if (c128) {
         if (mode == 0) HZ_UPD(double2, 0);
+        else if (point) HZ_UPDP(double2);
         else if (mode == 1) HZ_UPD(double2, 1);
         else HZ_UPD(double2, 2);
     } else {
         // pass 2 with the vectors split over the wavefronts where that measured faster (short
-        // bases, and bases too long for k_update's single-pass register form)
+        // bases, and bases too long for a point's vectors in registers)
         const bool pairs = (ldv & 1) == 0 && ((((uintptr_t)V) | ((uintptr_t)w)) & 15) == 0;
         if (mode == 1 && pairs && nv <= UPD_SPLIT4)
             hipLaunchKernelGGL((k_upd1_split<8, 4>), dim3(sp.nblk), dim3(256), 0, s, (const float2*)V, ldv, nv, h,
@@ -675,10 +753,12 @@ int launch_update(bool c128, const void* V, int64_t ldv, int nv, const double2* 
             hipLaunchKernelGGL((k_upd1_split<8, 8>), dim3(sp.nblk), dim3(512), 0, s, (const float2*)V, ldv, nv, h,
                                (float2*)w, n, sp.per_block, part, ldp, skip);
         else if (mode == 0) HZ_UPD(float2, 0);
+        else if (point) HZ_UPDP(float2);
         else if (mode == 1) HZ_UPD(float2, 1);
         else HZ_UPD(float2, 2);
     }
 #undef HZ_UPD
+#undef HZ_UPDP
     HZ_LAUNCH_CHECK();
     return HZ_OK;
 }

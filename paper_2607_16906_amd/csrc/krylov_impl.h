@@ -644,9 +644,22 @@ __device__ inline void arnoldi_lag_body(SolveState* st, double2* __restrict__ R,
     if (!tail) sc[3] = sc[2];
 }
 
-// y = R^{-1} g over the k completed columns (trailing zero pivots dropped).
-__device__ inline void backsolve_body(SolveState* st, const double2* R, const double2* g, double2* y) {
-    if (threadIdx.x != 0) return;
+// y = R^{-1} g over the k completed columns (trailing zero pivots dropped), one wavefront. Up to
+// BS_K columns the triangle lies in LDS and the lanes form the products of a solved entry side by
+// side; what stays serial is the order of each row's sum, l = i + 1 .. k - 1 (one thread with a load
+// from memory per term: 57 us at k = 30; this 29).
+constexpr int BS_K = 48;
+__device__ inline double2 bs_mul(double2 r, double2 y) {   // r y, the contraction spelled out
+    return double2{fma(r.x, y.x, -(r.y * y.y)), fma(r.y, y.x, r.x * y.y)};
+}
+__device__ inline double2 bs_div(double2 a, double2 d) {   // a / d
+    const double dd = fma(d.x, d.x, d.y * d.y);
+    return double2{fma(a.x, d.x, a.y * d.y) / dd, fma(a.y, d.x, -(a.x * d.y)) / dd};
+}
+__device__ inline void backsolve_body(SolveState* st, const double2* __restrict__ R, const double2* __restrict__ g,
+                                      double2* __restrict__ y) {
+    __shared__ double2 tri[BS_K * (BS_K + 1) / 2];   // column l at l (l + 1) / 2, rows 0 .. l
+    const int ln = threadIdx.x & 63;
     const int m = st->m;
     int k = st->k;
     if (st->flags & FL_NONFINITE) k = 0;
@@ -655,14 +668,30 @@ __device__ inline void backsolve_body(SolveState* st, const double2* R, const do
         if (d.x != 0.0 || d.y != 0.0) break;
         --k;
     }
-    for (int i = k - 1; i >= 0; --i) {
-        double2 acc = g[i];
-        for (int l = i + 1; l < k; ++l) acc = csub(acc, cmul(R[(int64_t)l * (m + 1) + i], y[l]));
-        const double2 d = R[(int64_t)i * (m + 1) + i];
-        const double dd = d.x * d.x + d.y * d.y;
-        y[i] = double2{(acc.x * d.x + acc.y * d.y) / dd, (acc.y * d.x - acc.x * d.y) / dd};
+    if (k <= BS_K) {
+#pragma unroll 8
+        for (int l = 0; l < k; ++l)
+            if (ln <= l) tri[l * (l + 1) / 2 + ln] = R[(int64_t)l * (m + 1) + ln];
+        const double2 gl = ln < k ? g[ln] : double2{0.0, 0.0};
+        __syncthreads();
+        for (int i = k - 1; i >= 0; --i) {
+            double2 acc{__shfl(gl.x, i, 64), __shfl(gl.y, i, 64)};
+#pragma unroll 8
+            for (int l = i + 1; l < k; ++l) acc = csub(acc, tri[l * (l + 1) / 2 + i]);
+            double2* const col = tri + i * (i + 1) / 2;
+            const double2 yi = bs_div(acc, col[i]);
+            if (ln == 0) y[i] = yi;
+            if (ln < i) col[ln] = bs_mul(col[ln], yi);
+            __syncthreads();
+        }
+    } else if (threadIdx.x == 0) {
+        for (int i = k - 1; i >= 0; --i) {
+            double2 acc = g[i];
+            for (int l = i + 1; l < k; ++l) acc = csub(acc, bs_mul(R[(int64_t)l * (m + 1) + i], y[l]));
+            y[i] = bs_div(acc, R[(int64_t)i * (m + 1) + i]);
+        }
     }
-    st->k = k;   // columns used by the x update
+    if (threadIdx.x == 0) st->k = k;   // columns used by the x update
 }
 
 }  // namespace hz
