@@ -344,6 +344,7 @@ static BatchPlan<P> batch_layout(int nsys, const hz_problem* const* probs, const
     const size_t es = c128 ? sizeof(double2) : sizeof(float2);
     Carver c(base, cap);
     B.S.resize(nsys);
+    SolveState* const states = c.take<SolveState>(nsys);   // together: the host reads them in one copy
     for (int s = 0; s < nsys; ++s) {
         const hz_problem* p = probs[s];
         SysLayout& L = B.S[s];
@@ -356,7 +357,7 @@ static BatchPlan<P> batch_layout(int nsys, const hz_problem* const* probs, const
         d.per = L.sp.per_block;
         d.nblk = L.sp.nblk;
         d.ldp = m + 2;
-        d.st = c.take<SolveState>(1);
+        d.st = states ? states + s : nullptr;
         d.R = c.take<double2>((size_t)(m + 1) * m);
         d.cs = c.take<double>(m);
         d.sn = c.take<double2>(m);
@@ -784,9 +785,8 @@ static int solve_batched(int nsys, const hz_problem* const* probs, const no_net*
         }
         std::vector<SolveState> hs(nsys);
         auto read_states = [&]() -> int {
-            for (int i = 0; i < nsys; ++i)
-                if (hipMemcpyAsync(&hs[i], B.S[i].d.st, sizeof(SolveState), hipMemcpyDeviceToHost, s) != hipSuccess)
-                    return HZ_ERR_HIP;
+            if (hipMemcpyAsync(hs.data(), B.S[0].d.st, sizeof(SolveState) * nsys, hipMemcpyDeviceToHost, s) != hipSuccess)
+                return HZ_ERR_HIP;
             return hipStreamSynchronize(s) == hipSuccess ? HZ_OK : HZ_ERR_HIP;
         };
         if (hipEventRecord(pt.ev[1], s) != hipSuccess) {
@@ -817,35 +817,50 @@ static int solve_batched(int nsys, const hz_problem* const* probs, const no_net*
                 if ((rc = upload_tables<P>(B, h, s)) != HZ_OK) break;
                 tables_dirty = true;
             }
-            if (tables_dirty || steps != graph_steps || !exec) {
-                const auto t0 = std::chrono::steady_clock::now();
+            // The first cycle of a set of tables and length is launched kernel by kernel; where another
+            // one like it may follow, its graph is captured beside it (the host's time, hidden by the
+            // card's).
+            const bool direct = tables_dirty || steps != graph_steps || !exec;
+            bool more = false;
+            for (int i : active) more |= hs[i].its + steps < o->maxit;
+            const auto t0 = std::chrono::steady_clock::now();
+            if (hipEventRecord(pt.ev[0], s) != hipSuccess) {
+                rc = HZ_ERR_HIP;
+                break;
+            }
+            if (direct) {
+                if ((rc = cycle_launches<P, C>(B, h, net, o->m, steps, s)) != HZ_OK) break;
+            } else if (hipGraphLaunch(exec, s) != hipSuccess) {
+                rc = HZ_ERR_HIP;
+                break;
+            }
+            if (hipEventRecord(pt.ev[1], s) != hipSuccess) {
+                rc = HZ_ERR_HIP;
+                break;
+            }
+            if (direct) {
                 if (exec) (void)hipGraphExecDestroy(exec);
                 if (graph) (void)hipGraphDestroy(graph);
                 exec = nullptr;
                 graph = nullptr;
-                if (hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal) != hipSuccess) {
-                    rc = HZ_ERR_HIP;
-                    break;
-                }
-                int crc = cycle_launches<P, C>(B, h, net, o->m, steps, s);
-                hipError_t e = hipStreamEndCapture(s, &graph);
-                if (crc != HZ_OK || e != hipSuccess ||
-                    hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0) != hipSuccess) {
-                    rc = crc != HZ_OK ? crc : HZ_ERR_HIP;
-                    if (rc == HZ_ERR_HIP) set_error("fgmres_solve_batched: graph capture failed");
-                    break;
+                if (more) {
+                    if (hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal) != hipSuccess) {
+                        rc = HZ_ERR_HIP;
+                        break;
+                    }
+                    int crc = cycle_launches<P, C>(B, h, net, o->m, steps, s);
+                    hipError_t e = hipStreamEndCapture(s, &graph);
+                    if (crc != HZ_OK || e != hipSuccess ||
+                        hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0) != hipSuccess) {
+                        rc = crc != HZ_OK ? crc : HZ_ERR_HIP;
+                        if (rc == HZ_ERR_HIP) set_error("fgmres_solve_batched: graph capture failed");
+                        break;
+                    }
                 }
                 graph_steps = steps;
                 tables_dirty = false;
-                pt.ms[HZ_PHASE_BUILD] +=
-                    std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
             }
-            if (hipEventRecord(pt.ev[0], s) != hipSuccess || hipGraphLaunch(exec, s) != hipSuccess ||
-                hipEventRecord(pt.ev[1], s) != hipSuccess) {
-                rc = HZ_ERR_HIP;
-                break;
-            }
-            if ((rc = read_states()) != HZ_OK || (rc = pt.add(HZ_PHASE_CYCLES)) != HZ_OK) break;
+            if ((rc = read_states()) != HZ_OK || (rc = pt.add_cycle(direct, t0)) != HZ_OK) break;
         }
         if (rc != HZ_OK) break;
         for (int i = 0; i < nsys; ++i) {

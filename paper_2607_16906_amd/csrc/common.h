@@ -2,10 +2,11 @@
 // float2/double2, BF16 conversion, wavefront reductions, error plumbing.
 #pragma once
 
+#include <algorithm>
+#include <chrono>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include <chrono>
 #include <string>
 
 #include "hz.h"
@@ -150,6 +151,17 @@ struct PhaseTimer {
         float t = 0.f;
         HZ_HIP(hipEventElapsedTime(&t, ev[0], ev[1]));
         ms[phase] += t;
+        return HZ_OK;
+    }
+    // the same for a cycle started at host time t0; build: its graph was captured beside it, what the
+    // host took beyond the GPU's time goes to HZ_PHASE_BUILD
+    int add_cycle(bool build, std::chrono::steady_clock::time_point t0) {
+        const double before = ms[HZ_PHASE_CYCLES];
+        HZ_TRY(add(HZ_PHASE_CYCLES));
+        if (build) {
+            const std::chrono::duration<double, std::milli> wall = std::chrono::steady_clock::now() - t0;
+            ms[HZ_PHASE_BUILD] += std::max(0.0, wall.count() - (ms[HZ_PHASE_CYCLES] - before));
+        }
         return HZ_OK;
     }
     ~PhaseTimer() {
