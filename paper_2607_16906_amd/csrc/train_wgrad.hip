@@ -73,6 +73,8 @@ struct WgBF16 {
     __device__ static f32x4_t mma(const Op& a, const Row& b, int dx, f32x4_t c) { return mma(a, b.v[dx], c); }
 };
 
+using S = WgBF16;
+
 // bytes of a plane of n pixels, padded so that the 8 lanes of one LDS store phase (16 bytes each,
 // the channels of a pixel, then the next pixel) hit different banks
 constexpr int wg_plane(int n, int pxb, int mod) { return (n * pxb + 127) / 128 * 128 + mod; }
@@ -117,15 +119,14 @@ __device__ __forceinline__ void wg_sum(f32x4_t (&acc)[N], unsigned char* lds, in
 
 // 3x3. Block: 32 WCO output x 16 WCI input channels, a wavefront 32 x 16 of them for all 9 taps (WK
 // wavefronts share those and split the rows). Tile: TW columns x 32 R / TW rows.
-template <class S, int WCO, int WCI, int WK, int R, int TW>
-__global__ __launch_bounds__(64 * WCO * WCI * WK, 2) void k_wgrad3(const WgradArgs<typename S::T> A) {
-    using T = typename S::T;
+template <int WCO, int WCI, int WK, int R, int TW>
+__global__ __launch_bounds__(64 * WCO * WCI * WK, 2) void k_wgrad3(const WgradArgs<bf16_t> A) {
     constexpr int NT = 64 * WCO * WCI * WK;
     constexpr int GC = TW / 8;                  // lane groups side by side
     constexpr int TH = 4 / GC * R, PW = TW + 2, PH = TH + 2;
     constexpr int CO = 32 * WCO, CI = 16 * WCI, RS = R / WK;
-    constexpr int PLG = wg_plane(TW * TH, S::PXB, CO >= 64 && S::VC == 8 ? 32 : 64);
-    constexpr int PLX = wg_plane(PW * PH, S::PXB, CI >= 64 && S::VC == 8 ? 32 : 64);
+    constexpr int PLG = wg_plane(TW * TH, S::PXB, CO >= 64 ? 32 : 64);
+    constexpr int PLX = wg_plane(PW * PH, S::PXB, CI >= 64 ? 32 : 64);
     constexpr int NVG = CO / S::VC, NVX = CI / S::VC;   // vectors per pixel
     constexpr int NG = (TW * TH * NVG + NT - 1) / NT, NX = (PW * PH * NVX + NT - 1) / NT;
     constexpr int LDS = PLG * (CO / 16) + PLX * (CI / 16);
@@ -196,8 +197,8 @@ __global__ __launch_bounds__(64 * WCO * WCI * WK, 2) void k_wgrad3(const WgradAr
     };
     // this lane group's place in the tile
     const int gy = (kg / GC) * R + wk * RS, gx = (kg % GC) * 8;
-    const typename S::Lane lg = S::lane(lds + wco * 2 * PLG, (gy * TW + gx) * S::PXB);
-    const typename S::Lane lx = S::lane(ldx + wci * PLX, (gy * PW + gx) * S::PXB);
+    const S::Lane lg = S::lane(lds + wco * 2 * PLG, (gy * TW + gx) * S::PXB);
+    const S::Lane lx = S::lane(ldx + wci * PLX, (gy * PW + gx) * S::PXB);
 
     const int t_beg = z * A.tpc, t_end = min(((rows + TH - 1) / TH) * tx_n, t_beg + A.tpc);
     if (t_beg < t_end) gload(t_beg);
@@ -206,13 +207,13 @@ __global__ __launch_bounds__(64 * WCO * WCI * WK, 2) void k_wgrad3(const WgradAr
         lstore();
         __syncthreads();
         if (tile + 1 < t_end) gload(tile + 1);
-        typename S::Row xr[3];
+        S::Row xr[3];
         xr[0] = S::row(lx, 0);
         xr[1] = S::row(lx, PW * S::PXB);
 #pragma unroll
         for (int s = 0; s < RS; ++s) {
             xr[(s + 2) % 3] = S::row(lx, (s + 2) * PW * S::PXB);
-            typename S::Op g[2];
+            S::Op g[2];
 #pragma unroll
             for (int k = 0; k < 2; ++k) g[k] = S::op(lg, s * TW * S::PXB + k * PLG);
 #pragma unroll
@@ -250,11 +251,10 @@ __global__ __launch_bounds__(64 * WCO * WCI * WK, 2) void k_wgrad3(const WgradAr
 // Transposed 2x2. Block: 32 output x 64 input channels, a wavefront 32 x 32 of them for the 4
 // parities; two wavefronts share those and split the rows. Tile: 16 columns x 2 R rows of coarse
 // pixels of the batch's B H rows; G is staged by parity, so that a run of coarse pixels is a run there.
-template <class S, int R>
-__global__ __launch_bounds__(256, 2) void k_wgradT(const WgradArgs<typename S::T> A) {
-    using T = typename S::T;
+template <int R>
+__global__ __launch_bounds__(256, 2) void k_wgradT(const WgradArgs<bf16_t> A) {
     constexpr int NT = 256, TW = 16, TH = 2 * R, CO = 32, CI = 64, WK = 2, RS = R / WK, NPX = TW * TH;
-    constexpr int PLG = wg_plane(NPX, S::PXB, S::VC == 8 ? 32 : 64), PLX = PLG;
+    constexpr int PLG = wg_plane(NPX, S::PXB, 32), PLX = PLG;
     constexpr int NVG = CO / S::VC, NVX = CI / S::VC;
     constexpr int NG = 4 * NPX * NVG / NT, NX = NPX * NVX / NT;
     static_assert(4 * NPX * NVG % NT == 0 && NPX * NVX % NT == 0 && RS >= 1, "whole vectors per thread");
@@ -317,7 +317,7 @@ __global__ __launch_bounds__(256, 2) void k_wgradT(const WgradArgs<typename S::T
         }
     };
     const int g = (((kg >> 1) * R + wk * RS) * TW + (kg & 1) * 8) * S::PXB;
-    const typename S::Lane lg = S::lane(lds, g), lx = S::lane(ldx + wci * 2 * PLX, g);
+    const S::Lane lg = S::lane(lds, g), lx = S::lane(ldx + wci * 2 * PLX, g);
 
     const int t_beg = z * A.tpc, t_end = min(((rows + TH - 1) / TH) * tx_n, t_beg + A.tpc);
     if (t_beg < t_end) gload(t_beg);
@@ -329,14 +329,14 @@ __global__ __launch_bounds__(256, 2) void k_wgradT(const WgradArgs<typename S::T
 #pragma unroll
         for (int s = 0; s < RS; ++s) {
             const int o = s * TW * S::PXB;
-            typename S::Op xb[2];
+            S::Op xb[2];
 #pragma unroll
             for (int i = 0; i < 2; ++i) xb[i] = S::op(lx, o + i * PLX);
 #pragma unroll
             for (int ab = 0; ab < 4; ++ab)
 #pragma unroll
                 for (int k = 0; k < 2; ++k) {
-                    const typename S::Op ga = S::op(lg, o + (ab * 2 + k) * PLG);
+                    const S::Op ga = S::op(lg, o + (ab * 2 + k) * PLG);
 #pragma unroll
                     for (int i = 0; i < 2; ++i)
                         acc[(ab * 2 + k) * 2 + i] = S::mma(ga, xb[i], acc[(ab * 2 + k) * 2 + i]);
@@ -606,47 +606,45 @@ unsigned wg_grid(const WgradArgs<T>& a) {
     return (unsigned)((a.nchunk >= 8 ? (a.nchunk + 7) / 8 * 8 : a.nchunk) * a.nct);
 }
 
-template <class S, int WCO, int WCI, int WK, int TW>
-int run3(WgradArgs<typename S::T>& a, int cap, hipStream_t s) {
-    constexpr int R = S::VC == 8 ? 8 : 4, TH = 32 * R / TW;
+template <int WCO, int WCI, int WK, int TW>
+int run3(WgradArgs<bf16_t>& a, int cap, hipStream_t s) {
+    constexpr int R = 8, TH = 32 * R / TW;
     const int ntiles = (a.B * (a.H + 1) + TH - 1) / TH * ((a.W + TW - 1) / TW);
     wg_chunks(a, ntiles, (a.cin_p + 16 * WCI - 1) / (16 * WCI) * ((a.cout_p + 32 * WCO - 1) / (32 * WCO)), cap);
-    hipLaunchKernelGGL((k_wgrad3<S, WCO, WCI, WK, R, TW>), dim3(wg_grid(a)), dim3(64 * WCO * WCI * WK), 0, s, a);
+    hipLaunchKernelGGL((k_wgrad3<WCO, WCI, WK, R, TW>), dim3(wg_grid(a)), dim3(64 * WCO * WCI * WK), 0, s, a);
     HZ_LAUNCH_CHECK();
     return HZ_OK;
 }
 
-template <class S, int WCO, int WCI, int WK>
-int run3w(WgradArgs<typename S::T>& a, int cap, hipStream_t s) {
+template <int WCO, int WCI, int WK>
+int run3w(WgradArgs<bf16_t>& a, int cap, hipStream_t s) {
     // 8 columns where 16 would cover more of nothing (W = 20: 24 columns, not 32)
-    return (a.W + 15) / 16 * 2 > (a.W + 7) / 8 ? run3<S, WCO, WCI, WK, 8>(a, cap, s)
-                                               : run3<S, WCO, WCI, WK, 16>(a, cap, s);
+    return (a.W + 15) / 16 * 2 > (a.W + 7) / 8 ? run3<WCO, WCI, WK, 8>(a, cap, s)
+                                               : run3<WCO, WCI, WK, 16>(a, cap, s);
 }
 
-template <class S>
-int conv3(WgradArgs<typename S::T>& a, int cap, hipStream_t s) {
+int conv3(WgradArgs<bf16_t>& a, int cap, hipStream_t s) {
     // the channel tile: 32 x 64 where the layer has them (both tensors are staged once per channel
     // tile of the other), 32 x 32, or 32 x 16 for the few channels of the first layer
-    if (a.cin_p <= 16) return run3w<S, 1, 1, 4>(a, cap, s);
-    if (a.cin_p % 64 == 0) return run3w<S, 1, 4, 1>(a, cap, s);
-    if (a.cout_p % 64 == 0) return run3w<S, 2, 2, 1>(a, cap, s);
-    return run3w<S, 1, 2, 2>(a, cap, s);
+    if (a.cin_p <= 16) return run3w<1, 1, 4>(a, cap, s);
+    if (a.cin_p % 64 == 0) return run3w<1, 4, 1>(a, cap, s);
+    if (a.cout_p % 64 == 0) return run3w<2, 2, 1>(a, cap, s);
+    return run3w<1, 2, 2>(a, cap, s);
 }
 
-template <class S>
-int convT(WgradArgs<typename S::T>& a, int cap, hipStream_t s) {
-    constexpr int R = S::VC == 8 ? 4 : 2, TH = 2 * R;
+int convT(WgradArgs<bf16_t>& a, int cap, hipStream_t s) {
+    constexpr int R = 4, TH = 2 * R;
     const int ntiles = (a.B * a.H + TH - 1) / TH * ((a.W + 15) / 16);
     wg_chunks(a, ntiles, (a.cin_p + 63) / 64 * ((a.cout_p + 31) / 32), cap);
-    hipLaunchKernelGGL((k_wgradT<S, R>), dim3(wg_grid(a)), dim3(256), 0, s, a);
+    hipLaunchKernelGGL((k_wgradT<R>), dim3(wg_grid(a)), dim3(256), 0, s, a);
     HZ_LAUNCH_CHECK();
     return HZ_OK;
 }
 
 }  // namespace
 
-int launch_wgrad3(WgradArgs<bf16_t>& a, int cap, hipStream_t s) { return conv3<WgBF16>(a, cap, s); }
-int launch_wgradT(WgradArgs<bf16_t>& a, int cap, hipStream_t s) { return convT<WgBF16>(a, cap, s); }
+int launch_wgrad3(WgradArgs<bf16_t>& a, int cap, hipStream_t s) { return conv3(a, cap, s); }
+int launch_wgradT(WgradArgs<bf16_t>& a, int cap, hipStream_t s) { return convT(a, cap, s); }
 
 int launch_wgrad3(WgradArgs<float>& a, int cap, hipStream_t s) {
     // about 1024 blocks, as many chunks as the partial buffer holds
