@@ -60,9 +60,10 @@ __global__ void k_spec_mmat(double2* __restrict__ Md, float2* __restrict__ Mf, c
     Mf[(int64_t)j * n + l] = float2{(float)m.x, (float)m.y};
 }
 
-// Matrix-core form. The two per-axis contractions are complex GEMMs, each taken as three real
-// 16 x 16 x 4 MFMA products per k-step (s1 += (a.re + a.im) b.re, s2 += a.re (b.im - b.re), s3 += a.im
-// (b.re + b.im); re = s1 - s3, im = s1 + s2).
+// Matrix-core form. The two per-axis contractions are complex GEMMs, each taken as four real
+// 16 x 16 x 4 MFMA products per k-step (re += a.re b.re - a.im b.im, im += a.re b.im + a.im b.re). Three products
+// (sums and differences of the parts, 10 % to 20 % faster at 1088^2) would do, but their sums have the size of
+// the larger part and cancel: with a part of 1e-2 of the other its error is 1e2 times as large.
 // A block of 8 wavefronts owns a (16 NB) x (16 NB) output tile; wavefronts 0-3 form the x part sum_k
 // u[y][k] Mx'[x][k], wavefronts 4-7 the y part sum_k My'[y][k] u[k][x], each over every fourth chunk
 // of SPK k values. Operands go from memory straight into registers, the next chunk's while the matrix
@@ -73,12 +74,12 @@ __global__ void k_spec_mmat(double2* __restrict__ Md, float2* __restrict__ Mf, c
 // part[tile]. Mx' = Mx and My' = My, or for ADJ Mx'[x][k] = conj(Mx[k][x]) and My'[y][k] =
 // conj(My[k][y]). FP32 takes v_mfma_f32_16x16x4_f32, FP64 v_mfma_f64_16x16x4_f64.
 //
-// 32 x 32 tiles are bound by the matrix cores (48 instructions per 4 operands of 16 k values); at small
-// grids the chain of a block's chunks takes the time, which 16 x 16 tiles with a quarter of the chunks
-// per wavefront shorten. Measured against 32 x 32 tiles staged in LDS, with four products per complex
-// product and one chain per part: 296^2 20.4 -> 10 us FP32, 30 -> 19 us FP64; 1088^2 234 -> 178 us FP32 (117
-// of 157 TFLOP/s, counting four products), 376 -> 365 us FP64. The error against 64 bits falls, too
-// (FP32, 1088^2: 7.1e-7 -> 4.0e-7), from the shorter sums.
+// 32 x 32 tiles are bound by the matrix cores (64 instructions per 4 operands of 16 k values) and the
+// rounds of tiles a CU takes one at a time; at small grids the chain of a block's chunks takes the time,
+// which 16 x 16 tiles with a quarter of the chunks per wavefront shorten. Measured against 32 x 32 tiles
+// staged in LDS with one chain per part: 296^2 20.2 -> 10.3 us FP32 (adjoint 23.2 -> 10.7), 30 -> 19 us FP64;
+// 1088^2 234 -> 216 us FP32 (95 of 157 TFLOP/s; adjoint 274 -> 226), 375 -> 388 us FP64 (adjoint 423 -> 388). The
+// error against 64 bits falls, too (FP32, 1088^2: 7.1e-7 -> 3.6e-7), from the shorter sums.
 constexpr int SPK = 16;     // k values per chunk
 constexpr int SPW = 512;    // threads per block
 
@@ -180,21 +181,21 @@ __global__ __launch_bounds__(SPW) void k_spectral(const C* __restrict__ u, C* __
             }
         }
     };
-    V s1[NB][NB], s2[NB][NB], s3[NB][NB];
+    V re[NB][NB], im[NB][NB];
 #pragma unroll
     for (int i = 0; i < NB; ++i)
 #pragma unroll
         for (int j = 0; j < NB; ++j)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) s1[i][j][r] = s2[i][j][r] = s3[i][j][r] = T(0);
+            for (int r = 0; r < 4; ++r) re[i][j][r] = im[i][j][r] = T(0);
     const int nch = (nk + SPK - 1) / SPK;
     // two operand sets in turn: one is loaded while the matrix cores work on the other
     C a0[NB][4], b0[NB][4], a1[NB][4], b1[NB][4];
     auto at = [&](int ch, C (&a)[NB][4], C (&bb)[NB][4]) {
         if (ch < nch) gload(ch * SPK + 4 * lg, (ch + 1) * SPK <= nk, a, bb);
     };
+    // (the conjugated matrix of ADJ: My' is the first operand of the y part, Mx' the second of the x part)
     auto compute = [&](C (&a)[NB][4], C (&bb)[NB][4]) {
-        // (the conjugated matrix: My' is the first operand of the y part, Mx' the second of the x part)
         if (ADJ) {
 #pragma unroll
             for (int i = 0; i < NB; ++i)
@@ -206,20 +207,19 @@ __global__ __launch_bounds__(SPW) void k_spectral(const C* __restrict__ u, C* __
         }
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
-            T as[NB], bd[NB], bs[NB];
-#pragma unroll
-            for (int i = 0; i < NB; ++i) {
-                as[i] = a[i][s].x + a[i][s].y;
-                bd[i] = bb[i][s].y - bb[i][s].x;
-                bs[i] = bb[i][s].x + bb[i][s].y;
-            }
 #pragma unroll
             for (int i = 0; i < NB; ++i)
 #pragma unroll
                 for (int j = 0; j < NB; ++j) {
-                    s1[i][j] = M::mma(as[i], bb[j][s].x, s1[i][j]);
-                    s2[i][j] = M::mma(a[i][s].x, bd[j], s2[i][j]);
-                    s3[i][j] = M::mma(a[i][s].y, bs[j], s3[i][j]);
+                    re[i][j] = M::mma(a[i][s].x, bb[j][s].x, re[i][j]);
+                    im[i][j] = M::mma(a[i][s].x, bb[j][s].y, im[i][j]);
+                }
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+#pragma unroll
+                for (int j = 0; j < NB; ++j) {
+                    re[i][j] = M::mma(-a[i][s].y, bb[j][s].y, re[i][j]);
+                    im[i][j] = M::mma(a[i][s].y, bb[j][s].x, im[i][j]);
                 }
         }
     };
@@ -244,8 +244,8 @@ __global__ __launch_bounds__(SPW) void k_spectral(const C* __restrict__ u, C* __
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int pos = M::row_of(lg, r) * 16 + lr;
-                red[wv][0][jj][pos] = s1[i][jj][r] - s3[i][jj][r];
-                red[wv][1][jj][pos] = s1[i][jj][r] + s2[i][jj][r];
+                red[wv][0][jj][pos] = re[i][jj][r];
+                red[wv][1][jj][pos] = im[i][jj][r];
             }
         __syncthreads();
         const int oy = y0 + 16 * i + (e >> 4), ox = x0 + 16 * j + (e & 15);
@@ -285,8 +285,8 @@ __global__ __launch_bounds__(SPW) void k_spectral(const C* __restrict__ u, C* __
 
 // Edge of a grid's tiles in 16 x 16 blocks: 2 or 1. A CU runs one block at a time, so a launch takes
 // its tiles in rounds of 256; a small tile takes about 6/5 of a quarter of a large one's time (fewer
-// matrix instructions per load): 544^2, 289 large tiles in two rounds 48 us, 1156 small ones in five
-// 38 us; 488^2, 256 large ones in one round 25 us, 961 small ones 26 us (FP32).
+// matrix instructions per load): 544^2, 289 large tiles in two rounds 49 us, 1156 small ones in five
+// 37 us; 488^2, 256 large ones in one round 25 us, 961 small ones 26 us (FP32; FP64 86, 67, 43 and 51 us).
 static int spectral_nb(const hz_problem* p) {
     auto rounds = [&](int te) {
         const int64_t t = (int64_t)((p->nxt + te - 1) / te) * ((p->nyt + te - 1) / te);
