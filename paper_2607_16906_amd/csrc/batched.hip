@@ -325,7 +325,7 @@ static bool head_fused(const no_net* net) {
     const int nl = (int)net->layers.size();
     if (net->a.levels < 2 || nl < 2) return false;
     const int cp = net->layers[nl - 2].cout_p;
-    return (cp == 16 || cp == 32 || cp == 64) && net->layers[nl - 1].cin_p == cp;
+    return head_fits(cp) && net->layers[nl - 1].cin_p == cp;
 }
 
 template <class P>

@@ -301,7 +301,7 @@ static int precond_impl(const no_net* net, const hz_problem* p, bool c128, const
         HZ_LAUNCH_CHECK();
         return HZ_OK;
     }
-    if (lh.cin_p == 16 || lh.cin_p == 32 || lh.cin_p == 64) {
+    if (head_fits(lh.cin_p)) {
         // the head runs in the epilogue of the last 3x3 layer
         Conv3Out hd;
         hd.head_w = packed_w<P>(net, lh);
@@ -524,7 +524,7 @@ static int autotune_impl(const no_net* net, int Hp, int Wp, int batch, const Fwd
         }
         if (rc == HZ_OK)
             rc = tune_layer(li + 2, (const T*)b.T1d[l], Ls[li + 2].cin_p, nullptr, 0, (T*)b.D[l], nullptr, H, W,
-                            nullptr, nullptr, l == 0 && batch == 1 && Ls[li + 2].cout_p <= 64);
+                            nullptr, nullptr, l == 0 && batch == 1 && head_fits(Ls[li + 2].cout_p));
         li += 3;
     }
     (void)hipEventDestroy(e0);

@@ -255,6 +255,10 @@ inline int paper8_body(const no_net* net, const FwdBufs& b, int Hp, int Wp, int 
     return HZ_OK;
 }
 
+// Whether the last 3x3 layer carries the 1x1 head in its epilogue: its stored channels are those of one
+// block of threads.
+inline bool head_fits(int cout_p) { return cout_p == 16 || cout_p == 32 || cout_p == 64; }
+
 // Whether level 0 runs as the fused encoder and decoder launches (net_level0.hip).
 template <class P>
 inline bool level0_fusable(const no_net* net) {
