@@ -171,12 +171,14 @@ int no_precond_apply(const no_net* net, const hz_problem* p, no_prec prec, hz_dt
 int no_precond_apply_noalloc(const no_net* net, const hz_problem* p, no_prec prec, hz_dtype dtype,
                              const void* v_dev, void* z_dev, void* stream);
 
-/* Time every launch variant (output-channel tile, pixel-tile height, input-channel chunks per
- * LDS stage) of every 3x3 layer at this problem's padded size and precision, on the forward
- * workspace ws_dev
- * (no_workspace_size bytes), and keep the fastest in the network handle; later forward passes
- * at that size use it. The variants accumulate every output in the same order, so the choice
- * never changes a result bit. fgmres_solve calls it on its first use of a size.
+/* Time the launch variants of every 3x3 layer at this problem's padded size and precision, on the
+ * forward workspace ws_dev (no_workspace_size bytes), and keep the fastest in the network handle;
+ * later forward passes at that size use it. Candidates are the streamed-weights forms that were
+ * the fastest somewhere (BF16 and FP32 layers of whole 32-channel chunks), the staged ones
+ * (output-channel tile, pixel-tile height, chunks per LDS stage) for the other layers, and the
+ * weight-stationary form. Level 0 is tuned layer by layer too: those choices are used where it does not
+ * run as two launches (no_set_fused_upsampling). The variants accumulate every output in the same
+ * order, so the choice never changes a result bit. fgmres_solve calls it on its first use of a size.
  * Synchronises `stream`; returns at once if the size was tuned before. Thread-safe. */
 int no_autotune(const no_net* net, const hz_problem* p, no_prec prec, void* ws_dev, size_t ws_bytes,
                 void* stream);
@@ -188,14 +190,17 @@ int no_autotune(const no_net* net, const hz_problem* p, no_prec prec, void* ws_d
  * its output channels in LDS across that many tiles; there *stages counts the tiles whose
  * patch loads are in flight together, 2 to 4), as no_autotune chose it or no_set_layer_variant
  * pinned it. A streamed-weights form (BF16 and FP32 layers of whole 32-channel chunks) reports its
- * own *tn (16 to 128) and *rows (2 to 16), *tiles 1 and a negative *stages that names it.
+ * own *tn (16 to 128) and *rows (2 to 16), *tiles 1 and a negative *stages that names it. The
+ * variants of level 0 are those of its layers as launches of their own (no_set_fused_upsampling).
  * Errors: NULL pointer, not a 3x3 layer. */
 int no_layer_variant(const no_net* net, int layer, no_prec prec, int batch, int H, int W, int32_t* tn,
                      int32_t* rows, int32_t* stages, int32_t* tiles);
 
 /* Pin the launch variant of 3x3 layer `layer` at (batch, H, W, prec) to (tn, rows, stages,
  * tiles), as if no_autotune had chosen it (a later no_autotune of that size keeps it). Every
- * variant gives the same result bits; this fixes the launch for profiling and measurement.
+ * variant gives the same result bits; this fixes the launch for profiling and measurement. A pinned
+ * layer of level 0 runs as a launch of its own, with the other layers of its half (the encoder's pair,
+ * or the transposed layer and the decoder's pair), whatever no_set_fused_upsampling chose.
  * Errors: not a 3x3 layer, tn not in {16, 32, 64} or not dividing the stored output channels,
  * rows not 8 or 16, stages not 1, or 2 / 4 for BF16 where that many chunk buffers fit in the
  * 160 KB of LDS of a workgroup (4 with tn 16, or tn 32 and 8 rows), tiles not 1, or 2..64 for
@@ -213,7 +218,8 @@ int no_set_layer_variant(const no_net* net, int layer, no_prec prec, int batch, 
  * level's first 3x3 convolution instead of storing it. mode 0: never; 1: always where it
  * applies; 2 (the default): where no_autotune measured it faster than the two separate layers
  * (untuned sizes run them separately). Modes 1 and 2 also run level 0 of a network with 32
- * base channels (BF16) as two launches, its encoder pair and its decoder with the output layer;
+ * base channels (BF16) as two launches, its encoder pair and its decoder with the output layer,
+ * each unless a 3x3 layer of it is pinned (no_set_layer_variant; fgmres_solve_batched knows no pins);
  * mode 0 runs every layer as its own launch. Every choice gives the same result bits. Not
  * thread-safe against concurrent solves on the handle. Errors: NULL network, mode not 0-2. */
 int no_set_fused_upsampling(no_net* net, int mode);

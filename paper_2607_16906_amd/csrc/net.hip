@@ -862,6 +862,7 @@ extern "C" int no_set_layer_variant(const no_net* net, int layer, no_prec prec, 
     c.ns = streamed ? 1 : stages;
     c.st = streamed ? -stages : 0;
     c.tpb = tiles > 1 ? tiles : 0;
+    c.pin = 1;
     mnet->tuned[{layer, H, W, batch, (int)prec}] = c;
     mnet->tune_gen.fetch_add(1);
     return HZ_OK;

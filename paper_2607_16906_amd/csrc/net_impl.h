@@ -287,14 +287,18 @@ inline int unet_body(const no_net* net, const FwdBufs& b, int Hp, int Wp, int ba
     const int lv = net->a.levels;
     const std::vector<Layer>& Ls = net->layers;
     int li = 0;
-    // (the fused-decoder choice covers this too: with 0 every layer is its own launch)
+    // (the fused-decoder choice covers this too: with 0 every layer is its own launch; and a half of the level
+    // with a pinned layer runs layer by layer)
     const bool fuse0 = head && batch == 1 && b.fuse_up != 0 && level0_fusable<P>(net);
+    const int n3 = (int)Ls.size() - 2;   // the last 3x3 layer
+    auto pinned = [&](int i) { return net_cfg(net, i, Hp, Wp, batch, prec_of<P>()).pin != 0; };
+    const bool enc0 = fuse0 && !pinned(0) && !pinned(1), dec0 = fuse0 && !pinned(n3 - 1) && !pinned(n3);
     for (int l = 0; l < lv; ++l) {
         const int H = Hp >> l, W = Wp >> l;
         const Layer& la = Ls[li++];
         const Layer& lb = Ls[li++];
         const T* in = l == 0 ? (const T*)b.X : (const T*)b.P[l];
-        if (l == 0 && fuse0) {
+        if (l == 0 && enc0) {
             if constexpr (std::is_same<P, PolBF16>::value)
                 HZ_TRY(launch_level0_enc(in, level0_enc(net), (T*)b.E[0], (T*)b.P[1], H, W, skip, s));
             continue;
@@ -311,7 +315,7 @@ inline int unet_body(const no_net* net, const FwdBufs& b, int Hp, int Wp, int ba
     const T* Dn = (const T*)b.E[lv - 1];
     for (int l = lv - 2; l >= 0; --l) {
         const int H = Hp >> l, W = Wp >> l;
-        if (l == 0 && fuse0) {
+        if (l == 0 && dec0) {
             if constexpr (std::is_same<P, PolBF16>::value)
                 HZ_TRY(launch_level0_dec((const T*)b.E[0], Dn, level0_dec(net), H, W, *head, skip, s));
             break;

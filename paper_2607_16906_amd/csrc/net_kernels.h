@@ -143,6 +143,7 @@ struct ConvCfg {
     int st = 0;     // > 0: streamed-weights form (conv3s_form); tn is then its channel tile
     int tpb = 0;    // > 1: weight-stationary form with tpb pixel tiles per block (BF16, conv3_ws_ok);
                     // ns is then the number of tiles whose loads are in flight (2, 3 or 4)
+    int pin = 0;    // set by no_set_layer_variant: the layer runs as a launch of its own
 };
 
 // LDS bytes of the weight-stationary 3x3 form: the weights of wch chunks and two patch buffers of

@@ -229,14 +229,16 @@ class Net:
         return z
 
     def autotune(self, problem: Problem, prec: str = "bf16"):
-        """Pick the fastest launch variant of every 3x3 layer at this problem's size (no_autotune)."""
+        """Pick the fastest launch variant of every 3x3 layer, as a launch of its own, at this problem's size
+        (no_autotune)."""
         lib = load_library()
         ws = _ws(lib.no_workspace_size(self.handle, problem.handle, PREC[prec]))
         _check(lib.no_autotune(self.handle, problem.handle, PREC[prec], _ptr(ws), ct.c_size_t(ws.numel()), _stream()),
                "no_autotune")
 
     def layer_variant(self, layer: int, H: int, W: int, prec: str = "bf16", batch: int = 1):
-        """(tn, rows, stages, tiles) launch variant of a 3x3 layer at this size (no_layer_variant)."""
+        """(tn, rows, stages, tiles) launch variant of a 3x3 layer, as a launch of its own, at this size
+        (no_layer_variant)."""
         tn, rows, st, tl = ct.c_int32(), ct.c_int32(), ct.c_int32(), ct.c_int32()
         _check(load_library().no_layer_variant(self.handle, layer, PREC[prec], batch, H, W, ct.byref(tn),
                                                ct.byref(rows), ct.byref(st), ct.byref(tl)), "no_layer_variant")
@@ -244,13 +246,15 @@ class Net:
 
     def set_layer_variant(self, layer: int, H: int, W: int, tn: int, rows: int, stages: int = 1, tiles: int = 1,
                           prec: str = "bf16", batch: int = 1):
-        """Pin the launch variant of a 3x3 layer at this size (no_set_layer_variant)."""
+        """Pin the launch variant of a 3x3 layer at this size (no_set_layer_variant); level 0 then runs the
+        layer's half layer by layer."""
         _check(load_library().no_set_layer_variant(self.handle, layer, PREC[prec], batch, H, W, tn, rows, stages,
                                                    tiles), "no_set_layer_variant")
 
     def set_fused_upsampling(self, mode: int):
         """BF16 decoder: transposed convolution inside the next 3x3 layer: 0 never, 1 always,
-        2 where autotuned faster (the default); the same result bits (no_set_fused_upsampling)."""
+        2 where autotuned faster (the default); and with 32 base channels level 0 as two launches (1, 2) or
+        layer by layer (0); the same result bits (no_set_fused_upsampling)."""
         _check(load_library().no_set_fused_upsampling(self.handle, int(mode)), "no_set_fused_upsampling")
 
     def layer_info(self, layer: int):

@@ -1,4 +1,8 @@
-"""The launch choices a caller sees: autotuning reaches the last 3x3 layer of every width."""
+"""The launch choices a caller sees: autotuning reaches the last 3x3 layer of every width, and a variant
+pinned for a level-0 layer is the launch that runs."""
+import ctypes
+
+import numpy as np
 import pytest
 
 from synth import H_10PPW, he_uniform, rng_for
@@ -23,3 +27,60 @@ def test_last_layer_is_tuned(base, prec):
     _, _, cout, _ = net.layer_info(last)
     tn = net.layer_variant(last, 32, 48, prec=prec)[0]
     assert tn > 0 and cout % tn == 0
+
+
+def workspace_after(net, gp, v):
+    """The bytes an application leaves in a workspace of 0xff bytes, and its result."""
+    import torch
+    from paper_2607_16906_amd import hz
+    lib = hz.load_library()
+    z = torch.empty_like(v)
+    ws = torch.full((lib.no_workspace_size(net.handle, gp.handle, hz.PREC["bf16"]),), 255, dtype=torch.uint8,
+                    device="cuda")
+    p = lambda t: ctypes.c_void_p(t.data_ptr())
+    assert lib.no_precond_apply(net.handle, gp.handle, hz.PREC["bf16"], hz.HZ_C64, p(v), p(z), p(ws),
+                                ctypes.c_size_t(ws.numel()),
+                                ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+    torch.cuda.synchronize()
+    return ws, z
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("pins", [[0], [1], [0, 1]])
+def test_pinned_encoder_layer_runs(pins):
+    # level 0 in two launches keeps the first layer's output out of the workspace; a pinned layer runs by itself
+    # and stores it
+    check_pins(pins, enc=True)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("pins", [[-2], [-1], [-2, -1]])   # the decoder's two 3x3 layers
+def test_pinned_decoder_layer_runs(pins):
+    check_pins(pins, enc=False)
+
+
+def check_pins(pins, enc):
+    import torch
+    from paper_2607_16906_amd import hz
+    net, gp = build(3, 32, 40, 24)
+    g = rng_for(103, 3, 0)
+    v = torch.from_numpy(g.standard_normal(gp.n) + 1j * g.standard_normal(gp.n)).to(torch.complex64).cuda()
+    last = len(hz.init_shapes(3, 32, 5)) - 2
+    net.set_fused_upsampling(0)
+    ws0, z0 = workspace_after(net, gp, v)
+    net.set_fused_upsampling(2)
+    ws2, z2 = workspace_after(net, gp, v)
+    untouched = [int((w == 255).sum()) for w in (ws0, ws2)]
+    assert untouched[1] > untouched[0] and torch.equal(z0, z2)   # the default mode stores less
+    for k in pins:
+        net.set_layer_variant(k if k >= 0 else last + 1 + k, 32, 48, 16, 8)
+    ws, z = workspace_after(net, gp, v)
+    assert torch.equal(z, z0)
+    part = int((ws == 255).sum())
+    assert part < untouched[1]
+    if enc:   # the upsampled tensor is still missing (the decoder stores it and shares the encoder's temporary)
+        assert part > untouched[0]
+    for k in range(2) if not enc else (last - 1, last):   # the other half too: every tensor is stored
+        net.set_layer_variant(k, 32, 48, 16, 8)
+    ws, z = workspace_after(net, gp, v)
+    assert torch.equal(z, z0) and torch.equal(ws, ws0)
