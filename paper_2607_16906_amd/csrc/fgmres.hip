@@ -20,6 +20,7 @@
 #include <cstring>
 #include <map>
 #include <mutex>
+#include <vector>
 
 #include "krylov.h"
 #include "net.h"
@@ -44,6 +45,14 @@ struct GraphKey {
     const void* ws;
     uint64_t ws_len;
 };
+// Keys of cycles that were launched directly and could not repeat in their solve: the last SEEN_MAX of them,
+// with the number of times.
+constexpr size_t SEEN_MAX = 64;
+struct SeenKey {
+    GraphKey key;
+    int times = 0;
+    uint64_t last = 0;
+};
 struct GraphKeyLess {
     bool operator()(const GraphKey& a, const GraphKey& b) const { return std::memcmp(&a, &b, sizeof a) < 0; }
 };
@@ -65,6 +74,10 @@ static std::map<GraphKey, KeptGraph, GraphKeyLess>& graph_cache() {
     return *c;
 }
 static uint64_t graph_stamp = 0;
+static std::vector<SeenKey>& graph_seen() {
+    static auto* v = new std::vector<SeenKey>();
+    return *v;
+}
 
 static void destroy_graph(hipGraph_t g, hipGraphExec_t e) {
     if (e) (void)hipGraphExecDestroy(e);
@@ -119,6 +132,32 @@ static bool graph_acquire(const GraphKey& k, GraphUse& u) {
     u.e = it->second.e;
     u.kept = true;
     return true;
+}
+
+// Whether a cycle about to be launched directly that cannot repeat in its solve (a solve of one cycle, or its last,
+// shorter one) is to be captured for later solves: from the third solve with the same arguments on. A solve on new
+// vectors would never replay the graph, which takes the host about as long as launching the cycle does and then a
+// place in the cache (one cycle of 12 steps without a network on 48^2 nodes: 0.69 ms with the capture, 0.64 without,
+// 0.57 replayed; 30 steps with one at 264^2: 4.65, 4.61 and 4.44, the capture hidden by the card's work).
+static bool graph_worth(const GraphKey& k) {
+    std::lock_guard<std::mutex> lk(graph_mu());
+    auto& v = graph_seen();
+    SeenKey* old = nullptr;
+    for (SeenKey& e : v) {
+        if (std::memcmp(&e.key, &k, sizeof k) == 0) {
+            e.last = ++graph_stamp;
+            return ++e.times > 2;
+        }
+        if (!old || e.last < old->last) old = &e;
+    }
+    if (v.size() < SEEN_MAX) {
+        v.emplace_back();
+        old = &v.back();
+    }
+    old->key = k;
+    old->times = 1;
+    old->last = ++graph_stamp;
+    return false;
 }
 
 // Keep a freshly instantiated graph (busy) if there is room, dropping the least recently used
@@ -317,14 +356,15 @@ static int solve_on(const hz_problem* p, const no_net* net, const hz_opts* o, co
         // one cycle = one graph launch; the graph of a cycle length is captured once (and kept
         // for later solves with the same arguments). The first cycle of a length does not wait for
         // its graph: it is launched kernel by kernel, and the capture (2.9 ms of host time for 30 steps
-        // at 296^2, whose 4.5 ms the card is then busy with) runs beside it.
+        // at 296^2, whose 4.5 ms the card is then busy with) runs beside it, if another cycle of the length
+        // may follow or the same solve keeps being called (graph_worth).
         auto cycle = [&]() {
             return o->ortho == 1 ? cycle_launches_lag(p, net, o, L, kb, b, x, steps, s)
                                  : cycle_launches(p, net, o, L, kb, b, x, steps, s);
         };
-        bool direct = false;
+        bool direct = false, capture = false;
         GraphKey k;
-        if (steps != graph_steps) {
+        if (steps != graph_steps || !gu.e) {
             gu.release();
             std::memset(&k, 0, sizeof k);
             k.puid = p->uid;
@@ -343,6 +383,7 @@ static int solve_on(const hz_problem* p, const no_net* net, const hz_opts* o, co
             k.ws = L.kb.st;   // the workspace base (the layout's first buffer)
             k.ws_len = L.total;
             direct = !graph_acquire(k, gu);
+            capture = direct && (hs.its + steps < o->maxit || graph_worth(k));
             graph_steps = steps;
         }
         const auto t0 = std::chrono::steady_clock::now();
@@ -350,7 +391,7 @@ static int solve_on(const hz_problem* p, const no_net* net, const hz_opts* o, co
         if (direct) HZ_TRY(cycle());
         else HZ_HIP(hipGraphLaunch(gu.e, s));
         HZ_HIP(hipEventRecord(pt.ev[1], s));
-        if (direct) {
+        if (capture) {
             HZ_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
             const int crc = cycle();
             const hipError_t e = hipStreamEndCapture(s, &gu.g);
@@ -361,7 +402,7 @@ static int solve_on(const hz_problem* p, const no_net* net, const hz_opts* o, co
         }
         HZ_HIP(hipMemcpyAsync(&hs, kb.st, sizeof(SolveState), hipMemcpyDeviceToHost, s));
         HZ_HIP(hipStreamSynchronize(s));
-        HZ_TRY(pt.add_cycle(direct, t0));
+        HZ_TRY(pt.add_cycle(capture, t0));
     }
     for (int i = 0; i < HZ_PHASE_TOTAL; ++i) info->phase_ms[i] = pt.ms[i];
     if (o->hist_host && o->hist_len > 0) {
