@@ -860,7 +860,7 @@ static int solve_batched(int nsys, const hz_problem* const* probs, const no_net*
                 graph_steps = steps;
                 tables_dirty = false;
             }
-            if ((rc = read_states()) != HZ_OK || (rc = pt.add_cycle(direct, t0)) != HZ_OK) break;
+            if ((rc = read_states()) != HZ_OK || (rc = pt.add_cycle(direct && more, t0)) != HZ_OK) break;
         }
         if (rc != HZ_OK) break;
         for (int i = 0; i < nsys; ++i) {

@@ -44,3 +44,11 @@ def test_cycles_that_may_repeat_are_captured_at_once():
     assert info.its == 25 and info.phase_ms["build"] > 0
     y, again = hz.fgmres(gp, b, m=10, tol=1e-14, maxit=25, krylov="c64", workspace=ws)
     assert torch.equal(x, y) and np.array_equal(info.hist, again.hist)
+
+
+@pytest.mark.gpu
+def test_batch_of_one_cycle_counts_no_capture():
+    from paper_2607_16906_amd import hz
+    sys_ = [system(nx, nx) for nx in (20, 33)]
+    _, infos = hz.fgmres_batched([gp for gp, _ in sys_], [b for _, b in sys_], m=8, tol=1e-14, maxit=8, krylov="c64")
+    assert all(i.its == 8 and i.phase_ms["build"] == 0 for i in infos)
