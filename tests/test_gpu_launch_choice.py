@@ -84,3 +84,26 @@ def check_pins(pins, enc):
         net.set_layer_variant(k, 32, 48, 16, 8)
     ws, z = workspace_after(net, gp, v)
     assert torch.equal(z, z0) and torch.equal(ws, ws0)
+
+
+@pytest.mark.gpu
+def test_forms_with_the_head_give_the_staged_bits():
+    # the last layer with the fused 1x1 head: the streamed forms that carry it (9 and 10 at 32 channels) against
+    # the staged form, on grids around their 8- and 16-row tiles
+    import torch
+    from paper_2607_16906_amd import hz
+    for nx, ny in ((40, 24), (5, 1), (9, 26), (70, 41)):
+        net, gp = build(3, 32, nx, ny)
+        net.set_fused_upsampling(0)
+        Hp, Wp = (ny + 11) // 4 * 4, (nx + 11) // 4 * 4
+        last = len(hz.init_shapes(3, 32, 5)) - 2
+        g = rng_for(103, 4, nx)
+        for prec in ("bf16", "fp32"):
+            for dt in (torch.complex64, torch.complex128):
+                v = torch.from_numpy(g.standard_normal(gp.n) + 1j * g.standard_normal(gp.n)).to(dt).cuda()
+                net.set_layer_variant(last, Hp, Wp, 32, 8, prec=prec)
+                ref = net.apply(gp, v, prec=prec)
+                assert float(ref.abs().max()) > 0
+                for fid, rows in ((9, 8), (10, 16)):
+                    net.set_layer_variant(last, Hp, Wp, 32, rows, -fid, 1, prec=prec)
+                    assert torch.equal(net.apply(gp, v, prec=prec), ref), (nx, ny, prec, fid)
