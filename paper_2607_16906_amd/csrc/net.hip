@@ -216,6 +216,18 @@ void net_padded_dims(const no_net* net, const hz_problem* p, int* Hp, int* Wp) {
 
 // ------------------------------------------------------------------ pack / head
 
+// sc[0] = s = ||v|| / sqrt(n) from norm partials, sc[1] = 1 / s (0 when s = 0): one block, k_pack's sum.
+constexpr unsigned PACK_SUM_BLOCKS = 8192;   // packing launches of up to so many blocks add the partials themselves
+__global__ __launch_bounds__(256) void k_scale_factor(const double2* __restrict__ part, int nblk, int ldp, int64_t n,
+                                                      double* __restrict__ sc, const int* __restrict__ skip) {
+    if (skip && *skip) return;
+    const double s = norm_scale(part, nblk, ldp, (double)n);
+    if (threadIdx.x == 0) {
+        sc[0] = s;
+        sc[1] = s > 0 ? 1.0 / s : 0.0;
+    }
+}
+
 // z = s (out_0 + i out_1), out_k = sum_c D0[c] Wh[k][c] + bh[k], on the grid only.
 template <class P, typename C>
 __global__ void k_head(const typename P::T* __restrict__ D, int cin_p, const typename P::T* __restrict__ wh,
@@ -266,8 +278,9 @@ static int precond_impl(const no_net* net, const hz_problem* p, bool c128, const
     Split sp = krylov_split(n);
     // s = ||v|| / sqrt(n); a unit-norm Krylov vector has s = 1 / sqrt(n) without a reduction
     const double fixed_s = unit_norm ? 1.0 / sqrt((double)n) : 0.0;
-    // otherwise the packing launch adds the norm's partial sums itself (every block the same few
-    // hundred values, in the same order: no launch for one block to do it)
+    // otherwise from the norm's partial sums, by the packing launch where it is short: every block adds the
+    // same few hundred values (1088^2: 14.3 us against 9.4 and 5.7 us for a launch of its own and the gap
+    // before it; 2400^2 51.8 against 32.9 and 5.7, 4096^2 150 against 87 and 5.9)
     NormParts own{b.part, sp.nblk, 1, b.sc};
     if (!unit_norm && !nparts) {
         HZ_TRY(launch_norm_partials(c128, v, n, sp, b.part, 1, 0, skip, s));
@@ -275,6 +288,12 @@ static int precond_impl(const no_net* net, const hz_problem* p, bool c128, const
     }
     double* scp = nparts ? nparts->sc : b.sc;   // [s, 1/s]
     const unsigned gp = (unsigned)(((int64_t)Hp * Wp + 255) / 256);
+    if (nparts && gp > PACK_SUM_BLOCKS) {
+        hipLaunchKernelGGL(k_scale_factor, dim3(1), dim3(256), 0, s, nparts->part, nparts->count, nparts->ldp, n, scp,
+                           skip);
+        HZ_LAUNCH_CHECK();
+        nparts = nullptr;
+    }
     if (c128)
         hipLaunchKernelGGL((k_pack<P, double2>), dim3(gp), dim3(256), 0, s, (const double2*)v, scp, p->cnd, p->sigx,
                            p->sigy, p->nxt, p->nyt, Hp, Wp, net->a.in_ch, (T*)b.X, skip, fixed_s, vscale,

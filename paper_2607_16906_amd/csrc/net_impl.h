@@ -59,6 +59,17 @@ __device__ __forceinline__ void pack_pixel(const C* __restrict__ v, double is, c
     for (int c = 0; c < 8; c += 16 / (int)sizeof(T)) *(uint4*)(dst + c) = *(const uint4*)(out + c);
 }
 
+// sqrt(the sum of the nnp partials / n), by a block of 256 threads.
+__device__ inline double norm_scale(const double2* __restrict__ part, int nnp, int ldp, double n) {
+    __shared__ double red[4];
+    double a = 0;
+    for (int q = threadIdx.x; q < nnp; q += 256) a += part[(int64_t)q * ldp].x;
+    a = wave_sum(a);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = a;
+    __syncthreads();
+    return sqrt((red[0] + red[1] + red[2] + red[3]) / n);
+}
+
 // One padded pixel per thread. fixed_s > 0: the caller knows ||v|| / sqrt(n) (a unit-norm Krylov
 // vector) and sc is not read; otherwise s = 1 / sc[1].
 template <class P, typename C>
@@ -76,14 +87,7 @@ __global__ void k_pack(const C* __restrict__ v, double* __restrict__ sc, const d
     double is;
     if (npart) {
         if (skipped) return;   // uniform over the block
-        __shared__ double red[4];
-        double a = 0;
-        for (int q = threadIdx.x; q < nnp; q += blockDim.x) a += npart[(int64_t)q * ldp].x;
-        a = wave_sum(a);
-        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = a;
-        __syncthreads();
-        const double nv2 = red[0] + red[1] + red[2] + red[3];
-        const double s = sqrt(nv2 / ((double)nxt * nyt));
+        const double s = norm_scale(npart, nnp, ldp, (double)nxt * nyt);
         is = s > 0 ? 1.0 / s : 0.0;
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             sc[0] = s;

@@ -1,0 +1,30 @@
+"""The network's input scale s = ||v|| / sqrt(n) on both sides of the grid size from which a launch of its own adds
+the norm's partial sums (2^21 padded pixels): a network of zero weights and a head bias of 1 returns s."""
+import numpy as np
+import pytest
+
+from synth import H_10PPW, rng_for
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("nx,ny", [(3, 5), (1440, 1440), (1444, 1440), (1500, 1501)])   # 8 more with the layers
+@pytest.mark.parametrize("dtype,prec", [("complex64", "fp32"), ("complex128", "fp64"), ("complex64", "bf16")])
+def test_scale(nx, ny, dtype, prec):
+    import torch
+    from paper_2607_16906_amd import hz
+    theta = np.zeros(hz.param_count(1, 8, 5), np.float32)
+    theta[-2] = 1.0
+    net = hz.Net(1, 8, 5, theta)
+    n = (nx + 8) * (ny + 8)
+    gp = hz.Problem(torch.full((n,), 1500.0), nx, ny, 4, H_10PPW)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    v = torch.randn(n, 2, generator=g, device="cuda", dtype=torch.float64)
+    v = torch.view_as_complex(v).to(getattr(torch, dtype))
+    v[::7] *= 1e3
+    s = float(torch.linalg.vector_norm(v.to(torch.complex128))) / np.sqrt(n)
+    z = net.apply(gp, v, prec=prec)
+    # every entry the same: s in FP64 sums (n 2^-53 at the worst), rounded once to the output's type
+    tol = 2.0 ** -23 if dtype == "complex64" else 1e-12
+    assert float((z.real - s).abs().max()) <= tol * s and float(z.imag.abs().max()) == 0
+    assert float((net.apply(gp, torch.zeros_like(v), prec=prec)).abs().max()) == 0
