@@ -310,7 +310,7 @@ __global__ __launch_bounds__(NW * 64) void k_upd1_split(const float2* __restrict
 // Pass 2 with one point per thread (ranges of KT points) and up to UPD_REG vectors, 8 at a time: w' from
 // all of them in order, then the sums, the last 8 from registers and the others read again (from the
 // caches). The same sums as k_update's register form, whose straight code for 32 vectors (27 KB, 336
-// registers) takes 20 us whatever nv; this 11.7 us for 25 to 30 vectors of 296^2 points.
+// registers) takes 20 us whatever nv; this 12 us for 25 to 30 vectors of 296^2 points.
 template <typename C>
 __global__ __launch_bounds__(KT) void k_upd1_point(const C* __restrict__ V, int64_t ldv, int nv,
                                                    const double2* __restrict__ h, C* __restrict__ w, int64_t n,
@@ -736,7 +736,10 @@ int launch_update(bool c128, const void* V, int64_t ldv, int nv, const double2* 
 #define HZ_UPDP(C)                                                                                       \
     hipLaunchKernelGGL(k_upd1_point<C>, dim3(sp.nblk), dim3(KT), 0, s, (const C*)V, ldv, nv, h, (C*)w, n, part, \
                        ldp, skip)
-    const bool point = mode == 1 && nv <= UPD_REG && sp.per_block == KT;   // else k_update's loop over points
+    // one point per thread: else k_update's loop over points. FP64 from the first vector on, against its loop
+    // with 32 vectors in registers: 296^2 12.7 -> 4.8 us with 1, 17.4 -> 9.9 with 24, 20.0 -> 13.1 with 32; 508^2
+    // 22.9 -> 6.1, 38.5 -> 27.6, 46.2 -> 38.0; 200^2 6.8 -> 4.2, 9.6 -> 9.1, 10.8 -> 11.0
+    const bool point = mode == 1 && nv <= UPD_REG && sp.per_block == KT;
     if (c128) {
         if (mode == 0) HZ_UPD(double2, 0);
         else if (point) HZ_UPDP(double2);
