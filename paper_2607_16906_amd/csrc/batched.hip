@@ -450,7 +450,7 @@ static void batch_conv3_form(const Layer& ly, int c1, int64_t tiles16, int64_t t
                              int& tn, int& rpw, int& tpb) {
     tpb = 0;
     const bool wide = std::is_same<P, PolBF16>::value && ly.cout_p % 32 == 0 && !head;
-    if (wide && !(st && (pool || ly.cin_p > P::CK)) && ws_jobs_ok<P>(ly.cin_p - c1, c1, ly.cout_p)) {
+    if (wide && !pool && ws_jobs_ok<P>(ly.cin_p - c1, c1, ly.cout_p)) {
         const int64_t ncb = ly.cout_p / WSJ_TN;
         int t = 32;
         while (t > 4 && (tiles16 + t - 1) / t * ncb < 1024) t /= 2;
@@ -676,9 +676,8 @@ static int net_step(const BatchPlan<P>& B, const HostTables<P>& h, const no_net*
                                             ly.cin_p, ly.cout_p, h.tn[li], s));
         } else if (h.ws[li]) {
             const int c1 = ly.cat_cp ? ly.cin_p - ly.cat_cp : 0;
-            const bool pool = role[li] == 1 && lvl[li] + 1 < net->a.levels;
             HZ_TRY(launch_conv3_ws_jobs<P>(t.cjobs[li], nj, t.io[li], packed_w<P>(net, ly), packed_b<P>(net, ly),
-                                           ly.cin_p - c1, c1, ly.cout_p, pool, s));
+                                           ly.cin_p - c1, c1, ly.cout_p, s));
         } else if (h.st[li]) {
             if constexpr (!std::is_same<P, PolF64>::value) {
                 const int c1 = ly.cat_cp ? ly.cin_p - ly.cat_cp : 0;

@@ -821,7 +821,7 @@ __global__ __launch_bounds__(WS_THREADS) void k_conv3_ws8(const typename P::T* _
 
 // Ragged batch, weight-stationary form: job = (system, first output channel, first tile, end
 // tile) in the fields (sys, c0, ty0, tx0).
-template <class P, int TN, bool POOL, int RPW, int WCH, int K, bool SMALL>
+template <class P, int TN, int RPW, int K, bool SMALL>
 __global__ __launch_bounds__(WS_THREADS) void k_conv3_ws_jobs(const TileJob* __restrict__ jobs,
                                                               const LayerIO* __restrict__ io,
                                                               const typename P::T* __restrict__ w,
@@ -830,9 +830,9 @@ __global__ __launch_bounds__(WS_THREADS) void k_conv3_ws_jobs(const TileJob* __r
     const TileJob jb = jobs[xcd_linear(blockIdx.x, gridDim.x)];
     const LayerIO d = io[jb.sys];
     if (d.stop && *d.stop) return;
-    conv3_ws_body<P, TN, POOL, RPW, WCH, K, SMALL>((const typename P::T*)d.x0, c0, (const typename P::T*)d.x1, c1, w, bias,
-                                                   (typename P::T*)d.y, cout_p, (typename P::T*)d.ypool, d.H, d.W, 1,
-                                                   jb.c0, jb.ty0, jb.tx0, 0);
+    conv3_ws_body<P, TN, false, RPW, 1, K, SMALL>((const typename P::T*)d.x0, c0, (const typename P::T*)d.x1, c1, w, bias,
+                                                  (typename P::T*)d.y, cout_p, nullptr, d.H, d.W, 1, jb.c0, jb.ty0,
+                                                  jb.tx0, 0);
 }
 
 // Decoder 3x3 convolution with the transposed convolution of the coarser level fused in (UpIn).
@@ -1629,21 +1629,18 @@ int launch_conv3_jobs_head(const TileJob* jobs, int njobs, const LayerIO* io, co
 
 template <class P>
 int launch_conv3_ws_jobs(const TileJob* jobs, int njobs, const LayerIO* io, const typename P::T* w,
-                         const typename P::Acc* bias, int c0, int c1, int cout_p, bool pool, hipStream_t s) {
+                         const typename P::Acc* bias, int c0, int c1, int cout_p, hipStream_t s) {
     if (njobs <= 0) return HZ_OK;
     if constexpr (std::is_same<P, PolBF16>::value) {
-        const int nch = (c0 + c1) / P::CK;
-        const bool small = conv3_ws_small<P>(c0, c1);
-        if (!ws_jobs_ok<P>(c0, c1, cout_p) || (small && pool)) {
-            set_error("conv3 jobs: the weight-stationary form needs BF16, 32-channel blocks, 1 or 2 input chunks");
+        if (!ws_jobs_ok<P>(c0, c1, cout_p)) {
+            set_error("conv3 jobs: the weight-stationary form needs BF16, 32-channel blocks, one input chunk");
             return HZ_ERR_ARG;
         }
-#define HZ_WSJ(PL, WC, SM)                                                                                          \
-    hipLaunchKernelGGL((k_conv3_ws_jobs<P, WSJ_TN, PL, WSJ_RPW, WC, 2, SM>), dim3(njobs), dim3(WS_THREADS), 0, s, jobs, \
-                       io, w, bias, c0, c1, cout_p)
-        if (small) HZ_WSJ(false, 1, true);
-        else if (nch == 1) { if (pool) HZ_WSJ(true, 1, false); else HZ_WSJ(false, 1, false); }
-        else { if (pool) HZ_WSJ(true, 2, false); else HZ_WSJ(false, 2, false); }
+#define HZ_WSJ(SM)                                                                                                \
+    hipLaunchKernelGGL((k_conv3_ws_jobs<P, WSJ_TN, WSJ_RPW, 2, SM>), dim3(njobs), dim3(WS_THREADS), 0, s, jobs, io, w, \
+                       bias, c0, c1, cout_p)
+        if (conv3_ws_small<P>(c0, c1)) HZ_WSJ(true);
+        else HZ_WSJ(false);
 #undef HZ_WSJ
         HZ_LAUNCH_CHECK();
         return HZ_OK;
@@ -1704,7 +1701,7 @@ int launch_convT2_jobs(const TileJob* jobs, int njobs, const LayerIO* io, const 
     template int launch_conv3_jobs_head<P>(const TileJob*, int, const LayerIO*, const P::T*, const P::Acc*, int,   \
                                            int, int, const P::T*, const P::Acc*, int, bool, hipStream_t);       \
     template int launch_conv3_ws_jobs<P>(const TileJob*, int, const LayerIO*, const P::T*, const P::Acc*, int, int, \
-                                         int, bool, hipStream_t);                                               \
+                                         int, hipStream_t);                                                     \
     template int launch_convT2_jobs<P>(const TileJob*, int, const LayerIO*, const P::T*, const P::Acc*, int, int, \
                                        int, hipStream_t);                                                      \
     template int launch_convT2_ws_jobs<P>(const TileJob*, int, const LayerIO*, const P::T*, const P::Acc*, int,    \

@@ -201,7 +201,8 @@ struct UpIn {
 constexpr int UP_CDMAX = 128;   // largest coarse channel count of the fused form
 
 // Streamed-weights 3x3 convolution (net_stream.h). Forms (id, 16-channel blocks per wavefront, rows
-// per wavefront, wavefronts along channels, wavefronts along rows).
+// per wavefront, wavefronts along channels, wavefronts along rows). 3, 6, 8 and 13 are never chosen (not once the
+// fastest by 3 %): they run where they are pinned, to measure against.
 #define HZ_CONV3S_FORMS(F) \
     F(1, 1, 2, 4, 1) F(2, 1, 4, 4, 1) F(3, 1, 8, 4, 1) F(4, 2, 8, 4, 1) F(5, 1, 4, 2, 2) F(6, 1, 8, 2, 2) F(7, 2, 4, 2, 2) \
     F(8, 2, 8, 2, 2) F(9, 2, 2, 1, 4) F(10, 2, 4, 1, 4) F(11, 1, 2, 2, 2) F(12, 1, 2, 1, 4) F(13, 1, 4, 1, 4)
@@ -417,17 +418,17 @@ template <class P>
 int launch_conv3_jobs_head(const TileJob* jobs, int njobs, const LayerIO* io, const typename P::T* w,
                            const typename P::Acc* bias, int c0, int c1, int cout_p, const typename P::T* head_w,
                            const typename P::Acc* head_b, int col, bool c128, hipStream_t s);
-// Weight-stationary form over a job table (BF16, inputs of one or two chunks or of one k-group per
-// tap; WSJ_TN output channels and 4 WSJ_RPW pixel rows per tile; job = (sys, first output channel, first tile, end tile) with tiles row-major over the
-// system's image).
+// Weight-stationary form over a job table (BF16, inputs of one chunk or of one k-group per tap, no pooled
+// output; WSJ_TN output channels and 4 WSJ_RPW pixel rows per tile; job = (sys, first output channel, first
+// tile, end tile) with tiles row-major over the system's image).
 constexpr int WSJ_TN = 32, WSJ_RPW = 4;
 template <class P>
 constexpr bool ws_jobs_ok(int c0, int c1, int cout_p) {
-    return conv3_ws_ok<P>(WSJ_TN, WSJ_RPW, c0, c1, cout_p) && c0 + c1 <= 2 * P::CK;
+    return conv3_ws_ok<P>(WSJ_TN, WSJ_RPW, c0, c1, cout_p) && c0 + c1 <= P::CK;
 }
 template <class P>
 int launch_conv3_ws_jobs(const TileJob* jobs, int njobs, const LayerIO* io, const typename P::T* w,
-                         const typename P::Acc* bias, int c0, int c1, int cout_p, bool pool, hipStream_t s);
+                         const typename P::Acc* bias, int c0, int c1, int cout_p, hipStream_t s);
 template <class P>
 int launch_convT2_jobs(const TileJob* jobs, int njobs, const LayerIO* io, const typename P::T* w,
                        const typename P::Acc* bias, int cin_p, int cout_p, int tn, hipStream_t s);

@@ -623,7 +623,9 @@ int run3w(WgradArgs<bf16_t>& a, int cap, hipStream_t s) {
                                                : run3<WCO, WCI, WK, 16>(a, cap, s);
 }
 
-int conv3(WgradArgs<bf16_t>& a, int cap, hipStream_t s) {
+}  // namespace
+
+int launch_wgrad3(WgradArgs<bf16_t>& a, int cap, hipStream_t s) {
     // the channel tile: 32 x 64 where the layer has them (both tensors are staged once per channel
     // tile of the other), 32 x 32, or 32 x 16 for the few channels of the first layer
     if (a.cin_p <= 16) return run3w<1, 1, 4>(a, cap, s);
@@ -632,7 +634,7 @@ int conv3(WgradArgs<bf16_t>& a, int cap, hipStream_t s) {
     return run3w<1, 2, 2>(a, cap, s);
 }
 
-int convT(WgradArgs<bf16_t>& a, int cap, hipStream_t s) {
+int launch_wgradT(WgradArgs<bf16_t>& a, int cap, hipStream_t s) {
     constexpr int R = 4, TH = 2 * R;
     const int ntiles = (a.B * a.H + TH - 1) / TH * ((a.W + 15) / 16);
     wg_chunks(a, ntiles, (a.cin_p + 63) / 64 * ((a.cout_p + 31) / 32), cap);
@@ -640,11 +642,6 @@ int convT(WgradArgs<bf16_t>& a, int cap, hipStream_t s) {
     HZ_LAUNCH_CHECK();
     return HZ_OK;
 }
-
-}  // namespace
-
-int launch_wgrad3(WgradArgs<bf16_t>& a, int cap, hipStream_t s) { return conv3(a, cap, s); }
-int launch_wgradT(WgradArgs<bf16_t>& a, int cap, hipStream_t s) { return convT(a, cap, s); }
 
 int launch_wgrad3(WgradArgs<float>& a, int cap, hipStream_t s) {
     // about 1024 blocks, as many chunks as the partial buffer holds
