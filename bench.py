@@ -36,7 +36,8 @@ WEIGHTS_SPEC = os.path.join(ROOT, "paper_2607_16906_amd", "weights", "unet_l4_c3
 WEIGHTS_L5 = os.path.join(ROOT, "paper_2607_16906_amd", "weights", "unet_l5_c32_in5.npz")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "conv3_dominant_layer_296_bf16_traffic.txt")
 GOLDEN_C2 = os.path.join(ROOT, "tests", "golden", "c2_oracle.json")
-KERNEL_SOURCES = [os.path.join(ROOT, "paper_2607_16906_amd", "csrc", f) for f in ("net_fwd.hip", "net_kernels.h")]
+KERNEL_SOURCES = [os.path.join(ROOT, "paper_2607_16906_amd", "csrc", f) for f in
+                  ("net_fwd.hip", "net_kernels.h", "net_stream.h", "net_stream_impl.h", "net_stream_bf16.hip")]
 
 
 def note(msg):
@@ -127,9 +128,36 @@ def net_layers(levels, base, in_ch, Hp, Wp):
     return out
 
 
+def launch_ms(torch, f, reps):
+    """Average time (ms) of f's launches back to back, HIP events: reps calls in one graph, as the solves run
+    them (called from Python one by one, launches of a few microseconds show the host's rate instead)."""
+    for _ in range(3):
+        f()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        for _ in range(reps):
+            f()
+    g.replay()
+    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    e0.record()
+    for _ in range(3):
+        g.replay()
+    e1.record()
+    torch.cuda.synchronize()
+    return e0.elapsed_time(e1) / (3 * reps)
+
+
+def in_level0(r, Hp):
+    """Whether a layer of the BF16 network runs inside the two launches of level 0 (the encoder's pair; the
+    transposed layer, the decoder's pair and the head), not as a launch of its own."""
+    return r["H"] == Hp or (r["kind"] == 1 and 2 * r["H"] == Hp)
+
+
 def time_layers(net, Hp, Wp, reps, prec="bf16", only=-1, levels=LEVELS):
-    """Per-layer average launch time (ms) with HIP events on the current stream, each layer with the
-    launch variant the autotuner chose for it (the one the solve uses)."""
+    """Per-layer average launch time (ms) with HIP events on the current stream, each layer as a launch of
+    its own with the variant the autotuner chose for it (the one the solve uses, but for the layers of
+    in_level0)."""
     import torch
     elem = {"bf16": torch.int16, "fp32": torch.float32}[prec]
     ws = torch.empty(4 * Hp * Wp * 32 * 4 + 256, dtype=torch.uint8, device="cuda")
@@ -143,15 +171,7 @@ def time_layers(net, Hp, Wp, reps, prec="bf16", only=-1, levels=LEVELS):
         x1 = torch.zeros(H * W * (cin_p - c0), dtype=elem, device="cuda") if cat_cp else None
         Ho, Wo = (H, W) if kind == 0 else (2 * H, 2 * W)
         y = torch.empty(Ho * Wo * cout_p, dtype=elem, device="cuda")
-        for _ in range(3):
-            net.layer_forward(i, x0, y, H=H, W=W, x1=x1, prec=prec, workspace=ws)
-        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-        e0.record()
-        for _ in range(reps):
-            net.layer_forward(i, x0, y, H=H, W=W, x1=x1, prec=prec, workspace=ws)
-        e1.record()
-        torch.cuda.synchronize()
-        ms = e0.elapsed_time(e1) / reps
+        ms = launch_ms(torch, lambda: net.layer_forward(i, x0, y, H=H, W=W, x1=x1, prec=prec, workspace=ws), reps)
         res.append(dict(layer=i, kind=kind, cin=cin, cout=cout, H=H, W=W, ms=ms,
                         flops=layer_flops(kind, cin, cout, H, W)))
     return res
@@ -162,16 +182,7 @@ def time_stencil(hz, torch, nt, reps=50):
     c = np.full(nt * nt, 1500.0, np.float32)
     p = hz.Problem(c, nt - 32, nt - 32, 16, 2 * np.pi / 10)
     x = torch.randn(nt * nt, dtype=torch.complex64, device="cuda")
-    for _ in range(3):
-        p.apply(x)
-    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-    e0.record()
-    for _ in range(reps):
-        y = p.apply(x)
-    e1.record()
-    torch.cuda.synchronize()
-    del y
-    return e0.elapsed_time(e1) / reps
+    return launch_ms(torch, lambda: p.apply(x), reps)
 
 
 def train_flops(levels, base, in_ch, Hp, Wp, batch):
@@ -724,13 +735,18 @@ def main():
         net.set_layer_variant(args.roofline_layer, lay[4], lay[5], tn, rows, stages, tiles)
     layers = time_layers(net, Hp, Wp, reps=50, only=args.roofline_layer if args.roofline_only else -1,
                          levels=levels)
-    dom = max(layers, key=lambda r: r["ms"])
+    # the largest of the launches that the solve makes (a profiler run of one layer: that layer)
+    dom = max([r for r in layers if not in_level0(r, Hp)] or layers, key=lambda r: r["ms"])
     tn, rows, stages, tiles = net.layer_variant(dom["layer"], dom["H"], dom["W"]) if dom["kind"] == 0 else (0, 0, 1, 1)
     variant = f"tn{tn} rows{rows}" + (f" stages{stages}" if stages > 1 else "") + (f" tiles{tiles}" if tiles > 1 else "")
+    if stages < 0:
+        variant += f" form{-stages}"
     achieved = dom["flops"] / (dom["ms"] * 1e-3) / 1e12
     net_ms = sum(r["ms"] for r in layers)
     net_flops = sum(r["flops"] for r in layers)
-    kname = "k_conv3<PolBF16, ...> (3x3 layer, autotuned variant)" if dom["kind"] == 0 else "k_convT2<PolBF16>"
+    kname = ("k_convT2s<StBF16, ...> (transposed layer)" if dom["kind"] == 1 else
+             ("k_conv3s<StBF16, ...>" if stages < 0 else "k_conv3_ws<PolBF16, ...>" if tiles > 1 else
+              "k_conv3<PolBF16, ...>") + " (3x3 layer, autotuned variant)")
     roofline = {"bound": "mfma", "achieved": round(achieved, 2), "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(achieved / PEAK_BF16_TFLOPS, 4), "traffic": measured_traffic(dom["layer"], variant),
                 "kernel": kname, "variant": variant, "layer": dom["layer"],
@@ -747,6 +763,9 @@ def main():
         return
 
     b = torch.from_numpy(s.b.ravel()).cuda()
+    # one application as the solve runs it (level 0 in two launches), packing and head included
+    v = (b / torch.linalg.vector_norm(b)).to(torch.complex64)
+    apply_ms = launch_ms(torch, lambda: net.apply(gp, v, "bf16"), 50)
     ws = torch.empty(hz.fgmres_workspace_bytes(gp, net, M_RESTART, MAXIT, "c64", "fp32"), dtype=torch.uint8,
                      device="cuda")
 
@@ -805,7 +824,8 @@ def main():
                       "vs_oracle": oracle_comparison(i32.its, i32.true_relres, "fp32_weights")},
         "speedup_bf16_vs_fp32": round(ms32 / ms_step, 3),
         "roofline": roofline,
-        "network": {"ms_per_apply_layers": round(net_ms, 4), "tflops_layers": round(net_flops / net_ms * 1e-9, 2),
+        "network": {"ms_per_apply": round(apply_ms, 4),
+                    "ms_per_apply_layers": round(net_ms, 4), "tflops_layers": round(net_flops / net_ms * 1e-9, 2),
                     "gflop_per_apply": round(net_flops * 1e-9, 3),
                     "layer_us": [[r["layer"], "conv3" if r["kind"] == 0 else "convT2", r["cin"], r["cout"], r["H"],
                                   round(r["ms"] * 1e3, 2)] for r in layers]},

@@ -12,10 +12,12 @@
 // operand pair per 16 clocks on each of 4 SIMDs). Here the same LDS feeds RPW rows of pixels to
 // NCB channel blocks: (RPW + 2) 3 reads for 9 RPW NCB instructions.
 //
-// Measured (BF16, best staged form -> streamed): 512 -> 256 channels at 136^2 64 -> 44 us (983
-// TFLOP/s, matrix-core bound), 64 -> 64 at 544^2 52 -> 35 us, 256 -> 128 at 64 x 40^2 98 -> 60 us, 256
-// -> 256 at 37^2 11.0 -> 7.8 us (latency of 8 chunks). FP32: 256 -> 128 at 32 x 24^2 139 -> 115 us
-// (95 of 157 TFLOP/s, with a quarter of the 16-pixel columns outside the image).
+// Measured (BF16, best staged form -> streamed): 512 -> 256 channels at 136^2 64 -> 44 us (983 TFLOP/s), 64 ->
+// 64 at 544^2 52 -> 35 us, 256 -> 128 at 64 x 40^2 98 -> 60 us, 256 -> 256 at 37^2 11.0 -> 7.8 us. FP32: 256 -> 128
+// at 32 x 24^2 139 -> 115 us (95 of 157 TFLOP/s, with a quarter of the 16-pixel columns outside the image).
+// What is left is latency: on large grids the matrix cores are busy for 31 to 38 % of the cycles and the LDS
+// for 20 to 25 %, with 2 to 3 wavefronts per SIMD that wait at one barrier per chunk; on small grids a block's
+// chain of chunks.
 #pragma once
 
 #include "net_kernels.h"
