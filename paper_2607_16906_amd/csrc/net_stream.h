@@ -3,7 +3,7 @@
 // A block of WC x WR wavefronts owns a (RPW WR) x 16 pixel tile and 16 NCB WC output channels;
 // wavefront (wc, wr) computes rows [RPW wr, RPW (wr + 1)) of 16 NCB channels. Only the input patch
 // goes through LDS. The weights come from memory straight into registers, packed in the order in
-// which a wavefront feeds them to the matrix cores (frag_index below: one 1 KB line per 16 x 32
+// which a wavefront feeds them to the matrix cores (conv3s_index: one 1 KB line per 16 x 32
 // operand), PF taps ahead of their use, so that no weight is staged, waited for at a barrier or
 // read back from LDS.
 //
