@@ -457,19 +457,10 @@ def bench_spectral(hz, torch, net):
         flops = 8.0 * (2 * s.nt) * n
         for dt, tag in ((torch.complex64, "fp32"), (torch.complex128, "fp64")):
             x = torch.randn(n, dtype=dt, device="cuda")
-            for _ in range(3):
-                gp.apply(x)
-            reps = 20 if name == "296" else 5
-            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-            e0.record()
-            for _ in range(reps):
-                y = gp.apply(x)
-            e1.record()
-            torch.cuda.synchronize()
-            ms = e0.elapsed_time(e1) / reps
+            ms = launch_ms(torch, lambda: gp.apply(x), 20 if name == "296" else 5)
             out[f"apply_{name}_{tag}_us"] = round(ms * 1e3, 2)
             out[f"apply_{name}_{tag}_tflops"] = round(flops / ms * 1e-9, 2)
-            del x, y
+            del x
         if name == "296":
             b = torch.from_numpy(s.b.ravel()).cuda()
             for key, nn in nets:
