@@ -308,7 +308,8 @@ enum {
     HZ_PHASE_CYCLES = 1,  /* GPU time of the restart cycles (network, matvec, Gram-Schmidt and
                              Hessenberg steps, cycle end with the FP64 true residual) */
     HZ_PHASE_BUILD = 2,   /* host time of the cycles whose graph is captured beside them, beyond
-                             their GPU time (zero when every cycle replays a kept graph) */
+                             their GPU time (zero when no graph is captured: every cycle
+                             replays a kept one, or cannot repeat and is launched directly) */
     HZ_PHASE_TOTAL = 3,   /* host wall time of the whole call */
     HZ_NPHASE = 4
 };

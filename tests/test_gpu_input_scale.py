@@ -28,3 +28,24 @@ def test_scale(nx, ny, dtype, prec):
     tol = 2.0 ** -23 if dtype == "complex64" else 1e-12
     assert float((z.real - s).abs().max()) <= tol * s and float(z.imag.abs().max()) == 0
     assert float((net.apply(gp, torch.zeros_like(v), prec=prec)).abs().max()) == 0
+
+
+@pytest.mark.gpu
+def test_lagged_orthogonalisation_above_the_limit():
+    # its partial sums come from the Gram-Schmidt pass: the same iterate as the reorthogonalised form, up to
+    # rounding (FP64, three steps)
+    import torch
+    from paper_2607_16906_amd import hz
+    from synth import he_uniform
+    nx = ny = 1500
+    n = (nx + 8) * (ny + 8)
+    net = hz.Net(1, 8, 5, he_uniform(hz.init_shapes(1, 8, 5), rng_for(131, 1, 0)))
+    gp = hz.Problem(torch.full((n,), 1500.0), nx, ny, 4, H_10PPW)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    b = torch.view_as_complex(torch.randn(n, 2, generator=g, device="cuda", dtype=torch.float64))
+    kw = dict(net=net, m=3, tol=1e-14, maxit=3, krylov="c128", net_prec="fp64")
+    x, info = hz.fgmres(gp, b, ortho="cgs2", **kw)
+    y, lag = hz.fgmres(gp, b, ortho="dcgs2", **kw)
+    assert info.its == lag.its == 3
+    assert float((x - y).norm()) <= 1e-9 * float(x.norm())
